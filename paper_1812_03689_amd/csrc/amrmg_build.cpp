@@ -531,8 +531,8 @@ static amrmg_status tag_level(amrmg_ctx *ctx, const HostLevel &L, int pos_dtype,
     A.lev[0] = dep_level(pr, L, G.bmap);
     A.rho[0] = rho;
     A.ncell[0] = G.nc;
-    launch_deposit(st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, perm, A, G.ub, (const int2 *)G.us, nout, cx, cy,
-                   cz, cq, big_tile(ctx, L.amr));
+    launch_deposit(st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, perm ? ctx->rec : nullptr, perm, A, G.ub, (const int2 *)G.us, nout, cx, cy,
+                   cz, cq, wide_tile(ctx, L.amr));
     tag_mark(ctx, G, rho, lambda);
     return tag_boxes(ctx, L, G, boxes);
 }
@@ -641,7 +641,7 @@ extern "C" amrmg_status amrmg_build_hierarchy(amrmg_ctx *ctx, int pos_dtype, con
     bool copy_done = !copied;
     auto ensure_copy = [&]() {
         if (copy_done) return;
-        launch_copy_ordered(ctx->st, pos_dtype == AMRMG_POS_F32, n, ctx->perm, x, y, z, q, (void *)tx, (void *)ty,
+        launch_copy_ordered(ctx->st, pos_dtype == AMRMG_POS_F32, n, ctx->perm, ctx->rec, x, y, z, q, (void *)tx, (void *)ty,
                             (void *)tz, (double *)tq);
         copy_done = true;
     };

@@ -1766,6 +1766,16 @@ __global__ void __launch_bounds__(1024) k_coarse_cycle(DevMeta M, const CoarseJo
 // ---------------------------------------------------------------------------
 // particles
 // ---------------------------------------------------------------------------
+// a / h, correctly rounded, from rh = 1/h rounded to nearest: with the
+// remainder a - h (a rh) exact in one fma, the corrected quotient is the
+// rounded one (Markstein's theorem), in 3 instructions instead of the
+// division's dozen
+__device__ __forceinline__ double div_by(double a, double h, double rh)
+{
+    const double q = a * rh;
+    return fma(fma(-q, h, a), rh, q);
+}
+
 template <class P>
 __device__ __forceinline__ bool cic_stencil(const DepLevel &D, double X, double Y, double Z, int *i0, int *i1,
                                             double *f)
@@ -1773,7 +1783,7 @@ __device__ __forceinline__ bool cic_stencil(const DepLevel &D, double X, double 
     double xs[3] = {X, Y, Z};
     for (int d = 0; d < 3; ++d) {
         if (!(xs[d] >= D.lo[d] && xs[d] < D.hi[d])) return false;
-        double s = (xs[d] - D.lo[d]) / D.h[d] - 0.5;
+        double s = div_by(xs[d] - D.lo[d], D.h[d], D.rh[d]) - 0.5;
         double fl = floor(s);
         int a = (int)fl;
         f[d] = s - fl;
@@ -1818,272 +1828,293 @@ __device__ __forceinline__ void spread_corners(const bool *st, V *v)
     v[7] = st[2] ? (st[1] ? (st[0] ? v[7] : v[6]) : v[5]) : v[3];
 }
 
-// Caller's-layout index of each corner of the CIC stencil (i0, i1) on level
-// D, -1 outside the level's boxes or for every corner when !ok.  Each
-// distinct brick of the stencil is looked up once (at most two per axis),
-// every lookup issued before any is used.
-__device__ __forceinline__ void corner_addresses(const DepLevel &D, const int64_t *ubase, const int2 *ustr, bool ok,
-                                                 const int *i0, const int *i1, int64_t (&u)[8])
-{
-    const bool st[3] = {(i0[0] >> 3) != (i1[0] >> 3), (i0[1] >> 3) != (i1[1] >> 3), (i0[2] >> 3) != (i1[2] >> 3)};
-    int g[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        g[c] = -1;
-        if (ok && corner_fresh(c, st)) {
-            const int bx = ((c & 1) ? i1[0] : i0[0]) >> 3, by = ((c & 2) ? i1[1] : i0[1]) >> 3,
-                      bz = ((c & 4) ? i1[2] : i0[2]) >> 3;
-            g[c] = D.bmap[bx + D.nbk[0] * (by + D.nbk[1] * bz)];
-        }
-    }
-    spread_corners(st, g);
-    int64_t ub[8];
-    int usx[8], usy[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        ub[c] = 0;
-        usx[c] = usy[c] = 0;
-        if (corner_fresh(c, st) && g[c] >= 0) {
-            ub[c] = ubase[g[c]];
-            const int2 s2 = ustr[g[c]];
-            usx[c] = s2.x;
-            usy[c] = s2.y;
-        }
-    }
-    spread_corners(st, ub);
-    spread_corners(st, usx);
-    spread_corners(st, usy);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int ii = (c & 1) ? i1[0] : i0[0], jj = (c & 2) ? i1[1] : i0[1], kk = (c & 4) ? i1[2] : i0[2];
-        u[c] = g[c] < 0 ? -1 : ub[c] + (ii & 7) + (int64_t)usx[c] * (jj & 7) + (int64_t)usy[c] * (kk & 7);
-    }
-}
-
-// Add v to rho[addr] for every active lane (addr >= 0), combining lanes of
-// the wavefront that share an address: up to 8 distinct addresses are summed
-// across the wavefront and issued as one atomic each by their first lane; the
-// remaining lanes issue their own atomics.
-__device__ __forceinline__ void wave_atomic_add(double *rho, int64_t addr, double v)
-{
-    const int lane = threadIdx.x & 63;
-    uint64_t active = __ballot(addr >= 0);
-    for (int round = 0; round < 8 && active; ++round) {
-        int leader = __builtin_ctzll(active);
-        int64_t A = __shfl(addr, leader, 64);
-        uint64_t match = __ballot(addr == A) & active;
-        double s = ((match >> lane) & 1) ? v : 0.0;
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (lane == leader) atomicAdd(rho + A, s);
-        active &= ~match;
-    }
-    if ((active >> lane) & 1) atomicAdd(rho + addr, v);
-}
-
-// Deposit every particle on every listed level.  A workgroup takes 256 PPT
+// Deposit every particle on every listed level.  A workgroup takes NT
 // consecutive particles of the visiting order (spatially sorted, so they are
 // close together) and, per level, accumulates their CIC weights in an LDS
 // tile over the bounding box of their stencils, then adds the tile's nonzero
-// cells to rho with one FP64 atomic each.  When the box exceeds the tile the
-// workgroup adds its weights with wavefront-combined global atomics instead.
-// Two tile sizes: 4096 cells (32 KB), and 8192 cells (64 KB, fewer
-// workgroups per CU) for levels on which a visiting-order bucket spans 8 or
-// more cells per axis, so that the boxes of those levels still fit (576^3
-// benchmark: deposit 8.7 -> 5.3 ms; on the levels with small buckets the
-// larger tile only costs occupancy).
-constexpr int DEP_TILE = 4096, DEP_TILE_BIG = 8192;
-// bricks whose layout a tile flush stages in LDS (a tile of 4096 cells spans
-// at most 4 x 4 x 4 bricks unless it is elongated; longer ones look up each cell)
-constexpr int DEP_BRICKS = 64;
-// particles from which a deposit launch takes the per-wavefront tile passes
-constexpr int64_t DEP_WAVES_MIN = (int64_t)4 << 20;
+// cells to rho with one FP64 atomic each.  When the box exceeds the tile
+// (sparse particles) each wavefront does the same alone, in its own part of
+// the tile over the box of its own particles; one whose box exceeds that too
+// adds every corner to rho by itself (then hardly any two are shared).
+//
+// Bounds: reading particles through the order (4e6 particles on 96^3 + 2
+// levels: about 305 of 362 us, from four arrays; now 32-byte records, the
+// whole deposit 183 us + 43 us to pack them); on dense levels the latency of
+// a workgroup's chain, so its registers and LDS are kept to six workgroups a
+// CU (9e6 particles on a level of 128^3 + 2, order kept: 209 -> 139 us, 1.5
+// us per 1e5); on sparse ones the memory side's atomics, about 12 64-byte
+// segments per nanosecond (1e7 particles on the finest level of 128^3 + 3:
+// 494 -> 331 us).
+// bricks whose layout a tile flush stages in LDS (a workgroup's tile; longer
+// boxes look up each cell, a wavefront's go corner by corner)
+constexpr int DEP_BRICKS = 64, DEP_WBRICKS = 32;
 
-// v[0..2] minima, v[3..5] maxima over the wavefront
-__device__ __forceinline__ void wave_minmax6(int *v)
+// minimum over the wavefront, in a scalar register
+__device__ __forceinline__ int wave_min(int v)
 {
-    for (int o = 32; o > 0; o >>= 1)
-        for (int a = 0; a < 6; ++a) {
-            int w = __shfl_xor(v[a], o, 64);
-            v[a] = a < 3 ? min(v[a], w) : max(v[a], w);
-        }
+#define AMRMG_DPP_MIN(ctrl, rmask) v = min(v, __builtin_amdgcn_update_dpp(INT_MAX, v, ctrl, rmask, 0xf, false))
+    AMRMG_DPP_MIN(0x111, 0xf);  // row_shr:1, 2, 4, 8: the minimum of each row of 16 lanes in its last lane
+    AMRMG_DPP_MIN(0x112, 0xf);
+    AMRMG_DPP_MIN(0x114, 0xf);
+    AMRMG_DPP_MIN(0x118, 0xf);
+    AMRMG_DPP_MIN(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+    AMRMG_DPP_MIN(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef AMRMG_DPP_MIN
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
-__device__ __forceinline__ void wg_minmax6(int *v, int *red)
-{
-    // v[0..2] minima, v[3..5] maxima over the workgroup of 256 threads
-    for (int o = 32; o > 0; o >>= 1)
-        for (int a = 0; a < 6; ++a) {
-            int w = __shfl_xor(v[a], o, 64);
-            v[a] = a < 3 ? min(v[a], w) : max(v[a], w);
-        }
-    const int wid = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0)
-        for (int a = 0; a < 6; ++a) red[a * 4 + wid] = v[a];
-    __syncthreads();
-    for (int a = 0; a < 6; ++a) {
-        int r = red[a * 4];
-        for (int k = 1; k < 4; ++k) r = a < 3 ? min(r, red[a * 4 + k]) : max(r, red[a * 4 + k]);
-        v[a] = r;
-    }
-    __syncthreads();
-}
-
-template <class P, int PPT, int TILE, bool WAVES>
-__global__ void __launch_bounds__(256) k_deposit(int64_t n, const P *x, const P *y, const P *z, const double *q,
-                                                 const uint32_t *perm, DepArgs A, const int64_t *ubase,
-                                                 const int2 *ustr, unsigned long long *nout, P *xs, P *ys, P *zs,
-                                                 double *qs)
-{
-    __shared__ double acc[TILE];
-    __shared__ int red[24];
-    // the caller's-layout base and strides of the bricks the tile spans
-    // (when they are at most DEP_BRICKS), looked up once per tile
-    __shared__ int64_t tub[DEP_BRICKS];
-    __shared__ int2 tus[DEP_BRICKS];
-    __shared__ int wbox[4][6];  // the wavefronts' boxes when the workgroup's exceeds the tile
-    const int64_t first = (int64_t)blockIdx.x * 256 * PPT;
-    double X[PPT], Y[PPT], Z[PPT], Q[PPT];
-    bool valid[PPT];
+// a box of cells [lo, hi] in LDS, x fastest, and the bricks it spans
+struct DepBox {
+    int lo[3], hi[3];
+    int ex, ey, ez;
+    int bx0, by0, bz0, nbx, nby, nbt;
+    int64_t vol;
+    // v: minima of i0 and of ~i1 per axis
+    __device__ __forceinline__ void set(const int *v)
+    {
 #pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        int64_t i = first + (int64_t)threadIdx.x * PPT + k;  // consecutive particles per thread
-        valid[k] = i < n;
-        int64_t p = valid[k] ? (perm ? (int64_t)perm[i] : i) : 0;
-        X[k] = valid[k] ? (double)x[p] : 0.0;
-        Y[k] = valid[k] ? (double)y[p] : 0.0;
-        Z[k] = valid[k] ? (double)z[p] : 0.0;
-        Q[k] = valid[k] ? q[p] : 0.0;
-        if (xs && valid[k]) {  // the visiting-order copy (exact: P -> double -> P)
-            xs[i] = (P)X[k];
-            ys[i] = (P)Y[k];
-            zs[i] = (P)Z[k];
-            qs[i] = Q[k];
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = v[d];
+            hi[d] = ~v[3 + d];
+        }
+        ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
+        vol = (int64_t)ex * ey * ez;
+        bx0 = lo[0] >> 3, by0 = lo[1] >> 3, bz0 = lo[2] >> 3;
+        nbx = (hi[0] >> 3) - bx0 + 1, nby = (hi[1] >> 3) - by0 + 1;
+        nbt = nbx * nby * ((hi[2] >> 3) - bz0 + 1);
+    }
+    __device__ __forceinline__ bool empty() const { return lo[0] > hi[0]; }
+    // caller's-layout base (-1 outside the level) and strides of brick t of the box
+    __device__ __forceinline__ void brick(const DepLevel &D, const int64_t *ubase, const int2 *ustr, int t, int64_t &ub,
+                                          int2 &us) const
+    {
+        const int r = t / nbx, iz = r / nby;
+        const int g = D.bmap[(bx0 + t - r * nbx) + D.nbk[0] * ((by0 + r - iz * nby) + D.nbk[1] * (bz0 + iz))];
+        ub = -1;
+        us = make_int2(0, 0);
+        if (g >= 0) {
+            ub = ubase[g];
+            us = ustr[g];
         }
     }
+    // the weights of one stencil into the tile: the 8 corners in an order
+    // that the lane number turns (its bits exchange lower and upper along the
+    // axes): the particles of a wavefront often share a stencil (the visiting
+    // order keeps them together), and the same corner of one cell from every
+    // lane at once would serialise the LDS atomics on one address
+    __device__ __forceinline__ void add(double *acc, const int *i0, const int *i1, const double *f, double qv) const
+    {
+        const int st[3] = {1, ex, ex * ey};
+        int o[3][2];
+        double w[3][2];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const bool sw = (threadIdx.x >> d) & 1;
+            const int u = (i1[d] - lo[d]) * st[d], v = (i0[d] - lo[d]) * st[d];
+            const double g = 1.0 - f[d];
+            o[d][0] = sw ? u : v;
+            o[d][1] = sw ? v : u;
+            w[d][0] = sw ? f[d] : g;
+            w[d][1] = sw ? g : f[d];
+        }
+#pragma unroll
+        for (int yz = 0; yz < 4; ++yz) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const double v = qv * (w[0][x] * w[1][yz & 1] * w[2][yz >> 1]);
+                atomicAdd(&acc[o[0][x] + (o[1][yz & 1] + o[2][yz >> 1])], v);
+            }
+        }
+    }
+    // the tile's nonzero cells t0, t0 + step, ... to rho; tub, tus: the bricks' table, or tub == nullptr
+    __device__ __forceinline__ void flush(const double *acc, int t0, int step, const int64_t *tub, const int2 *tus,
+                                          const DepLevel &D, const int64_t *ubase, const int2 *ustr, double *rho) const
+    {
+        // quotients by ex and ey through the reciprocal (exact: t is below
+        // 2^14, so (t + 1/2) / ex lies at least 1/(2 ex) from an integer, far
+        // more than the product's rounding)
+        const float rex = 1.0f / (float)ex, rey = 1.0f / (float)ey;
+        for (int t = t0; t < (int)vol; t += step) {
+            const double v = acc[t];
+            if (v == 0.0) continue;
+            const int r = (int)(((float)t + 0.5f) * rex), rz = (int)(((float)r + 0.5f) * rey);
+            const int ii = lo[0] + (t - r * ex), jj = lo[1] + (r - rz * ey), kk = lo[2] + rz;
+            int64_t u;
+            if (tub) {
+                const int k = ((ii >> 3) - bx0) + nbx * (((jj >> 3) - by0) + nby * ((kk >> 3) - bz0));
+                const int64_t b = tub[k];
+                const int2 s = tus[k];
+                u = b < 0 ? -1 : b + (ii & 7) + (int64_t)s.x * (jj & 7) + (int64_t)s.y * (kk & 7);
+            } else {
+                u = user_index(D, ubase, ustr, ii, jj, kk);
+            }
+            if (u >= 0) atomicAdd(rho + u, v);
+        }
+    }
+};
+
+// Corner by corner, for a wavefront whose particles lie too far apart for a
+// tile: per stencil row (y, z) both x cells of every particle, exchanged
+// through LDS so that neighbouring lanes take the two cells of one row -- the
+// memory side, which serves atomics by 64-byte segments and bounds this path,
+// then sees one request for both.  tab: 64 x 32 bytes of the wavefront's LDS.
+struct DepPair {
+    int64_t u;
+    double v;
+};
+__device__ __forceinline__ void dep_corners(const DepLevel &D, const int64_t *ubase, const int2 *ustr, DepPair *tab,
+                                            bool ok, const int *i0, const int *i1, const double *f, double qv,
+                                            double *rho)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int yz = 0; yz < 4; ++yz) {
+        const int j = (yz & 1) ? i1[1] : i0[1], k = (yz & 2) ? i1[2] : i0[2];
+        const double wy = (yz & 1) ? f[1] : 1.0 - f[1], wz = (yz & 2) ? f[2] : 1.0 - f[2];
+        DepPair a, b;
+        a.u = b.u = -1;
+        if (ok) {
+            const int row = D.nbk[0] * ((j >> 3) + D.nbk[1] * (k >> 3));
+            const int g0 = D.bmap[(i0[0] >> 3) + row], g1 = D.bmap[(i1[0] >> 3) + row];
+            if (g0 >= 0) {
+                const int2 s = ustr[g0];
+                a.u = ubase[g0] + (i0[0] & 7) + (int64_t)s.x * (j & 7) + (int64_t)s.y * (k & 7);
+            }
+            if (g1 >= 0) {
+                const int2 s = ustr[g1];
+                b.u = ubase[g1] + (i1[0] & 7) + (int64_t)s.x * (j & 7) + (int64_t)s.y * (k & 7);
+            }
+        }
+        a.v = qv * ((1.0 - f[0]) * wy * wz);
+        b.v = qv * (f[0] * wy * wz);
+        tab[2 * lane] = a;
+        tab[2 * lane + 1] = b;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        a = tab[lane];
+        b = tab[64 + lane];
+        __builtin_amdgcn_wave_barrier();
+        if (a.u >= 0) atomicAdd(rho + a.u, a.v);
+        if (b.u >= 0) atomicAdd(rho + b.u, b.v);
+    }
+}
+
+// REC: the particles come as records (x, y, z, q) in their own order and are
+// read through perm, one 32-byte read each; else as arrays, through perm when
+// it is given.  Read through the order from four arrays, a particle cost four
+// scattered 8-byte reads, which the memory side serves at the same rate as
+// 32-byte ones: first deposit of a build of 9e6 particles 604 -> 238 us (and
+// 68 us more for the keys, which write the records).
+template <class P, bool REC, int NT, int TILE>
+__global__ void __launch_bounds__(NT) k_deposit(int64_t n, const P *x, const P *y, const P *z, const double *q,
+                                                const double4 *rec, const uint32_t *perm, DepArgs A,
+                                                const int64_t *ubase, const int2 *ustr, unsigned long long *nout,
+                                                P *xs, P *ys, P *zs, double *qs)
+{
+    constexpr int NW = NT / 64, WTILE = TILE / NW;
+    __shared__ double acc[TILE];
+    __shared__ int box[2][6];  // this level's and the next's
+    __shared__ int64_t tub[NW * DEP_WBRICKS];
+    __shared__ int2 tus[NW * DEP_WBRICKS];
+    static_assert(NW * DEP_WBRICKS >= DEP_BRICKS && WTILE * sizeof(double) >= 128 * sizeof(DepPair), "LDS tables");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
+    const bool valid = i < n;
+    double X = 0.0, Y = 0.0, Z = 0.0, Q = 0.0;
+    if (valid) {
+        const int64_t p = perm ? (int64_t)perm[i] : i;
+        if (REC) {
+            const double4 r = rec[p];
+            X = r.x, Y = r.y, Z = r.z, Q = r.w;
+        } else {
+            X = (double)x[p], Y = (double)y[p], Z = (double)z[p], Q = q[p];
+        }
+        if (xs) {  // the visiting-order copy (exact: P -> double -> P)
+            xs[i] = (P)X;
+            ys[i] = (P)Y;
+            zs[i] = (P)Z;
+            qs[i] = Q;
+        }
+    }
+    if (threadIdx.x < 6) box[0][threadIdx.x] = INT_MAX;
+    __syncthreads();
     for (int l = 0; l < A.nlev; ++l) {
         const DepLevel &D = A.lev[l];
-        int i0[PPT][3], i1[PPT][3];
-        double f[PPT][3];
-        bool ok[PPT];
-        int bb[6] = {INT_MAX, INT_MAX, INT_MAX, INT_MIN, INT_MIN, INT_MIN};
+        int i0[3], i1[3];
+        double f[3];
+        const bool ok = valid && cic_stencil<P>(D, X, Y, Z, i0, i1, f);
+        if (l == 0 && nout) {
+            const uint64_t out = __ballot(valid && !ok);
+            if (out && lane == 0) atomicAdd(nout, (unsigned long long)__popcll(out));
+        }
+        const double qv = ok ? Q * D.ivol : 0.0;
+        int wv[6];
 #pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            ok[k] = valid[k] && cic_stencil<P>(D, X[k], Y[k], Z[k], i0[k], i1[k], f[k]);
-            if (valid[k] && !ok[k] && l == 0 && nout) atomicAdd(nout, 1ull);
-            if (ok[k])
-                for (int d = 0; d < 3; ++d) {
-                    bb[d] = min(bb[d], i0[k][d]);
-                    bb[3 + d] = max(bb[3 + d], i1[k][d]);
+        for (int d = 0; d < 3; ++d) {
+            wv[d] = wave_min(ok ? i0[d] : INT_MAX);
+            wv[3 + d] = wave_min(ok ? ~i1[d] : INT_MAX);
+        }
+        if (lane < 6) {
+            const int v = lane == 0 ? wv[0] : lane == 1 ? wv[1] : lane == 2 ? wv[2] : lane == 3 ? wv[3]
+                                                                                : lane == 4 ? wv[4] : wv[5];
+            atomicMin(&box[l & 1][lane], v);
+        }
+        __syncthreads();
+        int bv[6];
+#pragma unroll
+        for (int a = 0; a < 6; ++a) bv[a] = __builtin_amdgcn_readfirstlane(box[l & 1][a]);
+        if (threadIdx.x < 6) box[(l + 1) & 1][threadIdx.x] = INT_MAX;  // used after the next barrier
+        DepBox B;
+        B.set(bv);
+        if (B.vol <= TILE && !B.empty()) {
+            int64_t ub = -1;
+            int2 us = make_int2(0, 0);
+            const bool tab = B.nbt <= DEP_BRICKS;
+            if (tab && (int)threadIdx.x < B.nbt) B.brick(D, ubase, ustr, threadIdx.x, ub, us);
+            for (int t = threadIdx.x; t < (int)B.vol; t += NT) acc[t] = 0.0;
+            __syncthreads();
+            if (ok) B.add(acc, i0, i1, f, qv);
+            if (tab && (int)threadIdx.x < B.nbt) {
+                tub[threadIdx.x] = ub;
+                tus[threadIdx.x] = us;
+            }
+            __syncthreads();
+            B.flush(acc, threadIdx.x, NT, tab ? tub : nullptr, tus, D, ubase, ustr, A.rho[l]);
+        } else if (wv[0] != INT_MAX) {
+            B.set(wv);
+            double *wacc = acc + wave * WTILE;
+            if (B.vol <= WTILE && B.nbt <= DEP_WBRICKS) {
+                // the wavefront's own part of the tile and table: no barrier,
+                // the LDS accesses of one wavefront keep their order
+                int64_t *wub = tub + wave * DEP_WBRICKS, ub = -1;
+                int2 *wus = tus + wave * DEP_WBRICKS, us = make_int2(0, 0);
+                if (lane < B.nbt) B.brick(D, ubase, ustr, lane, ub, us);
+                for (int t = lane; t < (int)B.vol; t += 64) wacc[t] = 0.0;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                if (ok) B.add(wacc, i0, i1, f, qv);
+                if (lane < B.nbt) {
+                    wub[lane] = ub;
+                    wus[lane] = us;
                 }
-        }
-        // this lane's own bounds, kept for the wavefront boxes below
-        int lb[6];
-#pragma unroll
-        for (int a = 0; a < 6; ++a) lb[a] = bb[a];
-        wg_minmax6(bb, red);
-        if (bb[0] > bb[3]) continue;  // no particle of the workgroup inside the domain
-        // One pass through the LDS tile over the box tb of cells: clear, add
-        // the stencils of the taking part lanes' particles (mine), add the
-        // tile's nonzero cells to rho.  Every thread of the workgroup runs it.
-        auto tile_pass = [&](const int *tb, bool mine) {
-            const int ex = tb[3] - tb[0] + 1, ey = tb[4] - tb[1] + 1, ez = tb[5] - tb[2] + 1;
-            const int vol = ex * ey * ez;
-            for (int t = threadIdx.x; t < vol; t += 256) acc[t] = 0.0;
-            __syncthreads();
-            // the 8 corners of each stencil, in an order rotated by the
-            // lane: the particles of a wavefront often share a stencil (the
-            // visiting order keeps them together), and the same corner of
-            // one cell from every lane at once would serialise the LDS
-            // atomics on one address
-            const int rot = threadIdx.x & 7;
-#pragma unroll
-            for (int k = 0; k < PPT; ++k) {
-                if (!mine || !ok[k]) continue;
-                const double qv = Q[k] * D.ivol;
-                const int b = (i0[k][0] - tb[0]) + ex * ((i0[k][1] - tb[1]) + ey * (i0[k][2] - tb[2]));
-                const int ox = i1[k][0] - i0[k][0], oy = i1[k][1] - i0[k][1], oz = i1[k][2] - i0[k][2];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) {
-                    const int ce = (c + rot) & 7;
-                    const bool ux = ce & 1, uy = ce & 2, uz = ce & 4;
-                    const double w = (ux ? f[k][0] : 1.0 - f[k][0]) * (uy ? f[k][1] : 1.0 - f[k][1]) *
-                                     (uz ? f[k][2] : 1.0 - f[k][2]);
-                    atomicAdd(&acc[b + (ux ? ox : 0) + ex * ((uy ? oy : 0) + ey * (uz ? oz : 0))], qv * w);
-                }
-            }
-            // the tile's bricks: (bx0, by0, bz0) + (0..nbx-1, 0..nby-1, 0..nbz-1)
-            const int bx0 = tb[0] >> 3, by0 = tb[1] >> 3, bz0 = tb[2] >> 3;
-            const int nbx = (tb[3] >> 3) - bx0 + 1, nby = (tb[4] >> 3) - by0 + 1, nbz = (tb[5] >> 3) - bz0 + 1;
-            const int nbt = nbx * nby * nbz;
-            if (nbt <= DEP_BRICKS && (int)threadIdx.x < nbt) {
-                const int t = threadIdx.x, ix = t % nbx, iy = (t / nbx) % nby, iz = t / (nbx * nby);
-                const int g = D.bmap[(bx0 + ix) + D.nbk[0] * ((by0 + iy) + D.nbk[1] * (bz0 + iz))];
-                tub[t] = g >= 0 ? ubase[g] : -1;
-                tus[t] = g >= 0 ? ustr[g] : make_int2(0, 0);
-            }
-            __syncthreads();
-            for (int t = threadIdx.x; t < vol; t += 256) {
-                double v = acc[t];
-                if (v == 0.0) continue;
-                const int ii = tb[0] + t % ex, r = t / ex, jj = tb[1] + r % ey, kk = tb[2] + r / ey;
-                int64_t u;
-                if (nbt <= DEP_BRICKS) {
-                    const int k = ((ii >> 3) - bx0) + nbx * (((jj >> 3) - by0) + nby * ((kk >> 3) - bz0));
-                    const int64_t b = tub[k];
-                    const int2 us = tus[k];
-                    u = b < 0 ? -1 : b + (ii & 7) + (int64_t)us.x * (jj & 7) + (int64_t)us.y * (kk & 7);
-                } else {
-                    u = user_index(D, ubase, ustr, ii, jj, kk);
-                }
-                if (u >= 0) atomicAdd(A.rho[l] + u, v);
-            }
-            __syncthreads();
-        };
-        const int64_t vol = (int64_t)(bb[3] - bb[0] + 1) * (bb[4] - bb[1] + 1) * (bb[5] - bb[2] + 1);
-        if (vol <= TILE) {
-            tile_pass(bb, true);
-            continue;
-        }
-        // The stencils span more than the tile (sparse particles).  With
-        // WAVES the wavefronts take the tile in turn, each over the box of its
-        // own particles.  A wavefront whose box still exceeds the tile (every
-        // wavefront without WAVES) adds each corner with a global atomic, the
-        // addresses found first with every table load in flight together.
-        bool sparse = true;
-        if (WAVES) {
-            wave_minmax6(lb);
-            const int wave = threadIdx.x >> 6;
-            if ((threadIdx.x & 63) == 0)
-#pragma unroll
-                for (int a = 0; a < 6; ++a) wbox[wave][a] = lb[a];
-            __syncthreads();
-            sparse = false;  // this wavefront's box exceeds the tile too
-#pragma unroll 1
-            for (int wv = 0; wv < 4; ++wv) {
-                int tb[6];
-#pragma unroll
-                for (int a = 0; a < 6; ++a) tb[a] = wbox[wv][a];
-                if (tb[0] > tb[3]) continue;  // no particle of that wavefront inside the domain
-                const int64_t wvol = (int64_t)(tb[3] - tb[0] + 1) * (tb[4] - tb[1] + 1) * (tb[5] - tb[2] + 1);
-                if (wvol <= TILE) tile_pass(tb, wave == wv);
-                else if (wave == wv) sparse = true;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                B.flush(wacc, lane, 64, wub, wus, D, ubase, ustr, A.rho[l]);
+            } else {
+                dep_corners(D, ubase, ustr, (DepPair *)wacc, ok, i0, i1, f, qv, A.rho[l]);
             }
         }
-        if (!sparse) continue;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const double qv = ok[k] ? Q[k] * D.ivol : 0.0;
-            int64_t u[8];
-            corner_addresses(D, ubase, ustr, ok[k], i0[k], i1[k], u);
-            // all lanes stay in the loop: the combination uses wavefront shuffles
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                double w = ((c & 1) ? f[k][0] : 1.0 - f[k][0]) * ((c & 2) ? f[k][1] : 1.0 - f[k][1]) *
-                           ((c & 4) ? f[k][2] : 1.0 - f[k][2]);
-                wave_atomic_add(A.rho[l], u[c], qv * w);
-            }
-        }
+        __syncthreads();
     }
+}
+
+// the particles as records, in their own order
+template <class P>
+__global__ void __launch_bounds__(256) k_pack_records(int64_t n, const P *x, const P *y, const P *z, const double *q,
+                                                      double4 *rec)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) rec[i] = make_double4((double)x[i], (double)y[i], (double)z[i], q ? q[i] : 0.0);
 }
 
 // Two cells adjacent along x in one row of a box: one 16-byte load (8-byte
@@ -2450,44 +2481,49 @@ void launch_bottom_cg(hipStream_t st, const DevMeta &M, const int4 *jobs, int nj
     AMRMG_LAUNCH((k_bottom_cg<T>), dim3(njobs), dim3(1024), 0, st, M, jobs, rhs, e, work, rtol, maxit, iters);
 }
 
-template <class P, int PPT>
-static void launch_deposit_tile(hipStream_t st, unsigned g, bool big, int64_t n, const void *x, const void *y,
-                                const void *z, const double *q, const uint32_t *perm, const DepArgs &A,
-                                const int64_t *ubase, const int2 *ustr, unsigned long long *nout, void *xs, void *ys,
-                                void *zs, double *qs)
+template <class P, bool REC, int NT, int TILE>
+static void launch_deposit_t(hipStream_t st, int64_t n, const void *x, const void *y, const void *z, const double *q,
+                             const double4 *rec, const uint32_t *perm, const DepArgs &A, const int64_t *ubase,
+                             const int2 *ustr, unsigned long long *nout, void *xs, void *ys, void *zs, double *qs)
 {
-    // the per-wavefront tile passes for sparse workgroups: measured faster
-    // with 9e6 and 1e7 particles (128^3 + 2 and + 3 levels: deposit -10 %
-    // and -5 %), slower with 1e6 (64^3 + 2: +3 %, and +15 us in the build),
-    // where a launch is a few rounds of workgroups and the serial passes of
-    // the sparse ones lengthen it
-    const bool waves = n >= DEP_WAVES_MIN;
-#define AMRMG_DEPOSIT(TL, WV)                                                                                     \
-    AMRMG_LAUNCH((k_deposit<P, PPT, TL, WV>), dim3(g), dim3(256), 0, st, n, (const P *)x, (const P *)y,            \
-                 (const P *)z, q, perm, A, ubase, ustr, nout, (P *)xs, (P *)ys, (P *)zs, qs)
-    if (big) {
-        if (waves) AMRMG_DEPOSIT(DEP_TILE_BIG, true);
-        else AMRMG_DEPOSIT(DEP_TILE_BIG, false);
+    AMRMG_LAUNCH((k_deposit<P, REC, NT, TILE>), dim3(blocks_for(n, NT)), dim3(NT), 0, st, n, (const P *)x,
+                 (const P *)y, (const P *)z, q, rec, perm, A, ubase, ustr, nout, (P *)xs, (P *)ys, (P *)zs, qs);
+}
+
+void launch_deposit(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
+                    const double *q, const double4 *rec, const uint32_t *perm, const DepArgs &A, const int64_t *ubase,
+                    const int2 *ustr, unsigned long long *nout, void *xs, void *ys, void *zs, double *qs, bool wide)
+{
+    if (n <= 0 || A.nlev <= 0) return;
+    if (!perm) rec = nullptr;
+#define AMRMG_DEPOSIT(P, R)                                                                                       \
+    do {                                                                                                          \
+        if (wide)                                                                                                 \
+            launch_deposit_t<P, R, 512, 6144>(st, n, x, y, z, q, rec, perm, A, ubase, ustr, nout, xs, ys, zs, qs); \
+        else                                                                                                      \
+            launch_deposit_t<P, R, 256, 3072>(st, n, x, y, z, q, rec, perm, A, ubase, ustr, nout, xs, ys, zs, qs); \
+    } while (0)
+    if (pos_f32) {
+        if (rec) AMRMG_DEPOSIT(float, true);
+        else AMRMG_DEPOSIT(float, false);
     } else {
-        if (waves) AMRMG_DEPOSIT(DEP_TILE, true);
-        else AMRMG_DEPOSIT(DEP_TILE, false);
+        if (rec) AMRMG_DEPOSIT(double, true);
+        else AMRMG_DEPOSIT(double, false);
     }
 #undef AMRMG_DEPOSIT
 }
 
-void launch_deposit(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                    const double *q, const uint32_t *perm, const DepArgs &A, const int64_t *ubase, const int2 *ustr,
-                    unsigned long long *nout, void *xs, void *ys, void *zs, double *qs, bool big_tile)
+void launch_pack_records(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
+                         const double *q, double4 *rec)
 {
-    if (n <= 0 || A.nlev <= 0) return;
-    // one particle per thread: the most workgroups in flight measured fastest
-    // at 1e6 to 1e7 particles (ahead of two and four per thread, whose fewer
-    // tile flushes per particle do not make up for the lost parallelism)
-    const unsigned g = blocks_for(n, 256);
+    if (n <= 0) return;
+    const dim3 g(blocks_for(n, 256));
     if (pos_f32)
-        launch_deposit_tile<float, 1>(st, g, big_tile, n, x, y, z, q, perm, A, ubase, ustr, nout, xs, ys, zs, qs);
+        AMRMG_LAUNCH((k_pack_records<float>), g, dim3(256), 0, st, n, (const float *)x, (const float *)y,
+                     (const float *)z, q, rec);
     else
-        launch_deposit_tile<double, 1>(st, g, big_tile, n, x, y, z, q, perm, A, ubase, ustr, nout, xs, ys, zs, qs);
+        AMRMG_LAUNCH((k_pack_records<double>), g, dim3(256), 0, st, n, (const double *)x, (const double *)y,
+                     (const double *)z, q, rec);
 }
 
 template <class P, bool ORD>

@@ -11,6 +11,7 @@ constexpr int MAX_AMR = 8;
 // one AMR level as seen by particle kernels
 struct DepLevel {
     double lo[3], hi[3], h[3];
+    double rh[3];         // 1 / h
     double ivol;          // 1 / (h_x h_y h_z)
     int n[3];             // index extent of the level
     int nbk[3];           // brick grid extent (n / 8)
@@ -177,13 +178,17 @@ void launch_coarse_cycle(hipStream_t st, const DevMeta &M, const CoarseJob *jobs
 // with xs != nullptr, also the particles in visiting order (the order perm
 // gives; perm required): xs[i] = x[perm[i]], ... (the copy the ordered
 // deposits read later, written while the particles pass anyway).
-// big_tile: the larger LDS tile, for levels on which a visiting-order
-// bucket spans 8 or more cells per axis
+// rec: the particles as records in their own order (launch_pack_records),
+// read through perm instead of the arrays, or nullptr.  wide: the larger
+// workgroups and tiles, for levels finer than the visiting order
 void launch_deposit(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                    const double *q, const uint32_t *perm, const DepArgs &A, const int64_t *ubase, const int2 *ustr,
+                    const double *q, const double4 *rec, const uint32_t *perm, const DepArgs &A, const int64_t *ubase, const int2 *ustr,
                     unsigned long long *nout,
                     void *xs = nullptr, void *ys = nullptr, void *zs = nullptr, double *qs = nullptr,
-                    bool big_tile = false);
+                    bool wide = false);
+// rec[i] = (x, y, z, q) of particle i (q 0 when it is nullptr)
+void launch_pack_records(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
+                         const double *q, double4 *rec);
 void launch_zero_levels(hipStream_t st, const DepArgs &A);
 // ordered: x, y, z are already in the order perm gives (x[i] is particle
 // perm[i], the build's ordered copy); E is written at perm[i].  With perm,
@@ -200,16 +205,19 @@ void launch_fill(hipStream_t st, double *v, int64_t n, double val);
 // towards about four particles per cell but at most levels times, at most
 // 1024 cells per axis): perm [n] (perm[i] = the i-th particle visited) and
 // its inverse iperm [n]; scratch: order_scratch_bytes(n) bytes of device
-// memory
+// memory; with rec [n], also the particles as records (x, y, z, q) in their
+// own order
 size_t order_scratch_bytes(int64_t n);
 hipError_t particle_order(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                          const double *lo, const double *hi, const int *n0, int levels, void *scratch,
+                          const double *q, double4 *rec, const double *lo, const double *hi, const int *n0, int levels, void *scratch,
                           size_t scratch_bytes, uint32_t *perm, uint32_t *iperm);
 // log2 of the edge of a sort cell in level-0 cells (negative: finer than level 0)
 int order_cell_shift(const double *lo, const double *hi, const int *n0, int levels, int64_t n);
-// the particles in the visiting order alone: xs[i] = x[perm[i]], ...
-void launch_copy_ordered(hipStream_t st, int pos_f32, int64_t n, const uint32_t *perm, const void *x, const void *y,
-                         const void *z, const double *q, void *xs, void *ys, void *zs, double *qs);
+// the particles in the visiting order alone: xs[i] = x[perm[i]], ... (from
+// their records when rec is given)
+void launch_copy_ordered(hipStream_t st, int pos_f32, int64_t n, const uint32_t *perm, const double4 *rec,
+                         const void *x, const void *y, const void *z, const double *q, void *xs, void *ys, void *zs,
+                         double *qs);
 // proper nesting of the block marks of the finer level (g blocks per axis,
 // total = their product) against the coarse level (index extent cn, brick
 // map cbmap over cnbk bricks; half coarse cells per block edge, nesting by np

@@ -17,13 +17,19 @@
 #include "amrmg_state.hpp"
 
 
-// the deposit's larger LDS tile on levels where a cell of the visiting
-// order (that of the last build's particle count) spans 8 or more cells per
-// axis
-bool big_tile(const amrmg_ctx *ctx, int level)
+// The deposit's larger workgroups and tiles (512 particles over 6144 cells
+// instead of 256 over 3072) on levels where a cell of the visiting order
+// (that of the last build's particle count) spans four or more cells per
+// axis: the boxes of the smaller ones often exceed their tile there.  Finest
+// levels of 64^3 + 2 39 -> 34 us, 128^3 + 3 411 -> 331, 576^3 + 2 (three
+// levels in one launch) 708 -> 637; where a cell spans two the larger lose
+// (128^3 + 2 levels 151 -> 159 us), and with 1e5 particles, few workgroups,
+// they do too (8 -> 11 us).
+bool wide_tile(const amrmg_ctx *ctx, int level)
 {
-    const int64_t n = ctx->perm_n > 0 ? ctx->perm_n : 1;
-    return order_cell_shift(ctx->P.lo, ctx->P.hi, ctx->P.n0, ctx->P.max_level, n) + level >= 3;
+    constexpr int64_t kWideMin = (int64_t)1 << 18;
+    return ctx->perm_n >= kWideMin &&
+           order_cell_shift(ctx->P.lo, ctx->P.hi, ctx->P.n0, ctx->P.max_level, ctx->perm_n) + level >= 2;
 }
 
 DepLevel dep_level(const Problem &P, const HostLevel &L, const int32_t *bmap)
@@ -33,6 +39,7 @@ DepLevel dep_level(const Problem &P, const HostLevel &L, const int32_t *bmap)
         D.lo[d] = P.lo[d];
         D.hi[d] = P.hi[d];
         D.h[d] = L.h[d];
+        D.rh[d] = 1.0 / L.h[d];
         D.n[d] = L.n[d];
         D.nbk[d] = L.nbk[d];
     }
@@ -54,6 +61,7 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
     ctx->perm = nullptr;
     ctx->iperm = nullptr;
     ctx->perm_n = -1;
+    ctx->rec = nullptr;
     if (n <= 0 || n > (int64_t)0x7fffffff) return AMRMG_OK;
     const amrmg_params &P = ctx->P;
     const size_t sb = order_scratch_bytes(n);
@@ -71,7 +79,11 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
         cz = cy + align256((size_t)n * ps);
     }
     uint32_t *perm = (uint32_t *)ctx->sort_vals.p;
-    HIP_TRY(particle_order(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, P.lo, P.hi, P.n0, P.max_level,
+    if (ctx->rec_own.ensure(sizeof(double4) * (size_t)n) == hipSuccess)
+        ctx->rec = (double4 *)ctx->rec_own.p;
+    else
+        (void)hipGetLastError();
+    HIP_TRY(particle_order(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->rec, P.lo, P.hi, P.n0, P.max_level,
                            ctx->sort_scratch.p, ctx->sort_scratch.cap, perm, perm + n));
     ctx->perm = perm;
     ctx->iperm = perm + n;
@@ -83,6 +95,20 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
         *qs = cq;
     }
     return AMRMG_OK;
+}
+
+// Records of moved particles that are visited in the last build's order, or
+// nullptr to read the arrays through the order.  Packing them costs a launch
+// and 64 bytes a particle, the four scattered reads it saves about 17 ns per
+// thousand particles each: 4e6 particles 305 -> 123 us, 1e6 68 -> 33 us, 3e5
+// 13.1 -> 10.4 us, where a launch more is no longer worth it.
+constexpr int64_t kPackMin = (int64_t)1 << 19;
+static const double4 *moved_records(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,
+                                    const double *q, int64_t n)
+{
+    if (n < kPackMin || ctx->perm_n != n || !ctx->rec) return nullptr;
+    launch_pack_records(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->rec);
+    return ctx->rec;
 }
 
 extern "C" amrmg_status amrmg_deposit(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,
@@ -111,10 +137,11 @@ extern "C" amrmg_status amrmg_deposit(amrmg_ctx *ctx, int pos_dtype, const void 
     launch_zero_levels(ctx->st, A);
     int64_t cells = 0;
     for (int l = 0; l < A.nlev; ++l) cells += A.ncell[l];
+    const double4 *rec = moved_records(ctx, pos_dtype, x, y, z, q, n);
     ctx->prof.begin(AMRMG_K_DEPOSIT);
-    launch_deposit(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->perm_n == n ? ctx->perm : nullptr, A,
-                   ctx->ds.M.ubase, ctx->ds.M.ustr, dout, nullptr, nullptr, nullptr, nullptr,
-                   big_tile(ctx, pr.namr() - 1));
+    launch_deposit(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, rec, ctx->perm_n == n ? ctx->perm : nullptr,
+                   A, ctx->ds.M.ubase, ctx->ds.M.ustr, dout, nullptr, nullptr, nullptr, nullptr,
+                   wide_tile(ctx, pr.namr() - 1));
     ctx->prof.end(AMRMG_K_DEPOSIT, (double)n * (3.0 * (pos_dtype == AMRMG_POS_F32 ? 4 : 8) + 8.0) + 8.0 * (double)cells);
     HIP_TRY(hipGetLastError());
     if (n_outside) {
@@ -170,8 +197,8 @@ extern "C" amrmg_status amrmg_deposit_built(amrmg_ctx *ctx, double *const *rho, 
         int64_t cells = 0;
         for (int l = 0; l < A.nlev; ++l) cells += A.ncell[l];
         ctx->prof.begin(AMRMG_K_DEPOSIT);
-        launch_deposit(ctx->st, pos == AMRMG_POS_F32, n, xs, ys, zs, qs, nullptr, A, ctx->ds.M.ubase, ctx->ds.M.ustr,
-                       dout, nullptr, nullptr, nullptr, nullptr, big_tile(ctx, finest));
+        launch_deposit(ctx->st, pos == AMRMG_POS_F32, n, xs, ys, zs, qs, nullptr, nullptr, A, ctx->ds.M.ubase, ctx->ds.M.ustr,
+                       dout, nullptr, nullptr, nullptr, nullptr, wide_tile(ctx, finest));
         ctx->prof.end(AMRMG_K_DEPOSIT, (double)n * (3.0 * ps + 8.0) + 8.0 * (double)cells);
     }
     HIP_TRY(hipGetLastError());

@@ -94,10 +94,12 @@ static size_t sort_align(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // keys of the particles (a particle outside the domain takes the nearest
 // cell: the deposit skips it wherever it is visited) and the histogram of
-// their lowest digit per tile, hist[digit * tiles + tile]
+// their lowest digit per tile, hist[digit * tiles + tile]; with rec, also the
+// particles as records (x, y, z, q) in their own order
 template <class P, int DB, int IT>
-__global__ void __launch_bounds__(RADIX_NT) k_sort_keys(int64_t n, const P *x, const P *y, const P *z, SortGrid G,
-                                                        int tiles, uint32_t *key, uint32_t *hist)
+__global__ void __launch_bounds__(RADIX_NT) k_sort_keys(int64_t n, const P *x, const P *y, const P *z,
+                                                        const double *q, double4 *rec, SortGrid G, int tiles,
+                                                        uint32_t *key, uint32_t *hist)
 {
     constexpr int BINS = 1 << DB;
     __shared__ uint32_t h[BINS];
@@ -108,6 +110,7 @@ __global__ void __launch_bounds__(RADIX_NT) k_sort_keys(int64_t n, const P *x, c
         const int64_t p = base + r * RADIX_NT + threadIdx.x;
         if (p >= n) break;
         const double X[3] = {(double)x[p], (double)y[p], (double)z[p]};
+        if (rec) rec[p] = make_double4(X[0], X[1], X[2], q[p]);
         uint32_t k = 0;
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -254,12 +257,21 @@ __global__ void __launch_bounds__(RADIX_NT) k_radix_scatter(int64_t n, const uin
 // the particles in visiting order (random reads, coalesced writes: faster
 // than scattering them with the order)
 template <class P>
-__global__ void __launch_bounds__(256) k_copy_ordered(int64_t n, const uint32_t *perm, const P *x, const P *y,
-                                                      const P *z, const double *q, P *xs, P *ys, P *zs, double *qs)
+__global__ void __launch_bounds__(256) k_copy_ordered(int64_t n, const uint32_t *perm, const double4 *rec, const P *x,
+                                                      const P *y, const P *z, const double *q, P *xs, P *ys, P *zs,
+                                                      double *qs)
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     const uint32_t p = perm[i];
+    if (rec) {
+        const double4 r = rec[p];
+        xs[i] = (P)r.x;
+        ys[i] = (P)r.y;
+        zs[i] = (P)r.z;
+        qs[i] = r.w;
+        return;
+    }
     xs[i] = x[p];
     ys[i] = y[p];
     zs[i] = z[p];
@@ -310,15 +322,15 @@ size_t order_scratch_bytes(int64_t n) { return n > 0 ? sort_scratch(n, nullptr).
 
 template <int DB, int IT>
 static hipError_t sort_passes(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                              const SortGrid &G, const SortScratch &S, uint32_t *perm, uint32_t *iperm)
+                              const double *q, double4 *rec, const SortGrid &G, const SortScratch &S, uint32_t *perm, uint32_t *iperm)
 {
     const int tiles = radix_tiles(n), passes = radix_passes(G);
     if (pos_f32)
         hipLaunchKernelGGL((k_sort_keys<float, DB, IT>), dim3(tiles), dim3(RADIX_NT), 0, st, n, (const float *)x,
-                           (const float *)y, (const float *)z, G, tiles, S.ka, S.hist);
+                           (const float *)y, (const float *)z, q, rec, G, tiles, S.ka, S.hist);
     else
         hipLaunchKernelGGL((k_sort_keys<double, DB, IT>), dim3(tiles), dim3(RADIX_NT), 0, st, n, (const double *)x,
-                           (const double *)y, (const double *)z, G, tiles, S.ka, S.hist);
+                           (const double *)y, (const double *)z, q, rec, G, tiles, S.ka, S.hist);
     const uint32_t *kin = S.ka, *vin = nullptr;
     for (int pass = 0; pass < passes; ++pass) {
         const int shift = DB * pass;
@@ -338,7 +350,7 @@ static hipError_t sort_passes(hipStream_t st, int pos_f32, int64_t n, const void
 }
 
 hipError_t particle_order(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                          const double *lo, const double *hi, const int *n0, int levels, void *scratch,
+                          const double *q, double4 *rec, const double *lo, const double *hi, const int *n0, int levels, void *scratch,
                           size_t scratch_bytes, uint32_t *perm, uint32_t *iperm)
 {
     if (n <= 0) return hipSuccess;
@@ -347,29 +359,29 @@ hipError_t particle_order(hipStream_t st, int pos_f32, int64_t n, const void *x,
     const SortScratch S = sort_scratch(n, scratch);
     const bool large = radix_items(n) == ITEMS_LARGE;
     switch (radix_digit(G)) {
-    case 6: return large ? sort_passes<6, ITEMS_LARGE>(st, pos_f32, n, x, y, z, G, S, perm, iperm)
-                         : sort_passes<6, ITEMS_SMALL>(st, pos_f32, n, x, y, z, G, S, perm, iperm);
-    case 7: return large ? sort_passes<7, ITEMS_LARGE>(st, pos_f32, n, x, y, z, G, S, perm, iperm)
-                         : sort_passes<7, ITEMS_SMALL>(st, pos_f32, n, x, y, z, G, S, perm, iperm);
-    case 8: return large ? sort_passes<8, ITEMS_LARGE>(st, pos_f32, n, x, y, z, G, S, perm, iperm)
-                         : sort_passes<8, ITEMS_SMALL>(st, pos_f32, n, x, y, z, G, S, perm, iperm);
-    case 9: return large ? sort_passes<9, ITEMS_LARGE>(st, pos_f32, n, x, y, z, G, S, perm, iperm)
-                         : sort_passes<9, ITEMS_SMALL>(st, pos_f32, n, x, y, z, G, S, perm, iperm);
-    default: return large ? sort_passes<10, ITEMS_LARGE>(st, pos_f32, n, x, y, z, G, S, perm, iperm)
-                          : sort_passes<10, ITEMS_SMALL>(st, pos_f32, n, x, y, z, G, S, perm, iperm);
+    case 6: return large ? sort_passes<6, ITEMS_LARGE>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm)
+                         : sort_passes<6, ITEMS_SMALL>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm);
+    case 7: return large ? sort_passes<7, ITEMS_LARGE>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm)
+                         : sort_passes<7, ITEMS_SMALL>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm);
+    case 8: return large ? sort_passes<8, ITEMS_LARGE>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm)
+                         : sort_passes<8, ITEMS_SMALL>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm);
+    case 9: return large ? sort_passes<9, ITEMS_LARGE>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm)
+                         : sort_passes<9, ITEMS_SMALL>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm);
+    default: return large ? sort_passes<10, ITEMS_LARGE>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm)
+                          : sort_passes<10, ITEMS_SMALL>(st, pos_f32, n, x, y, z, q, rec, G, S, perm, iperm);
     }
 }
 
-void launch_copy_ordered(hipStream_t st, int pos_f32, int64_t n, const uint32_t *perm, const void *x, const void *y,
-                         const void *z, const double *q, void *xs, void *ys, void *zs, double *qs)
+void launch_copy_ordered(hipStream_t st, int pos_f32, int64_t n, const uint32_t *perm, const double4 *rec,
+                         const void *x, const void *y, const void *z, const double *q, void *xs, void *ys, void *zs, double *qs)
 {
     if (n <= 0) return;
     const unsigned g = (unsigned)((n + 255) / 256);
     if (pos_f32)
-        hipLaunchKernelGGL((k_copy_ordered<float>), dim3(g), dim3(256), 0, st, n, perm, (const float *)x,
+        hipLaunchKernelGGL((k_copy_ordered<float>), dim3(g), dim3(256), 0, st, n, perm, rec, (const float *)x,
                            (const float *)y, (const float *)z, q, (float *)xs, (float *)ys, (float *)zs, qs);
     else
-        hipLaunchKernelGGL((k_copy_ordered<double>), dim3(g), dim3(256), 0, st, n, perm, (const double *)x,
+        hipLaunchKernelGGL((k_copy_ordered<double>), dim3(g), dim3(256), 0, st, n, perm, rec, (const double *)x,
                            (const double *)y, (const double *)z, q, (double *)xs, (double *)ys, (double *)zs, qs);
 }
 

@@ -317,6 +317,12 @@ struct amrmg_ctx {
     // deposit; any order gives the same sums up to rounding)
     DBuf sort_scratch, sort_vals;  // the sort's work space; the order and its inverse
     DBuf sorted;  // the particles of the last build in visiting order (charges, x, y, z)
+    // the particles as records in their own order: written with the sort keys
+    // by a build, or from the caller's arrays by a deposit or gather of moved
+    // particles, and read through the order (one scattered read a particle);
+    // without room the arrays themselves are read through the order
+    DBuf rec_own;
+    double4 *rec = nullptr;
     uint32_t *perm = nullptr;
     uint32_t *iperm = nullptr;  // its inverse (perm[iperm[p]] == p)
     int64_t perm_n = -1;
@@ -363,7 +369,7 @@ struct SolveOpts {
 amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Problem *> &probs, bool direct);
 
 // amrmg_particles.cpp
-bool big_tile(const amrmg_ctx *ctx, int level);
+bool wide_tile(const amrmg_ctx *ctx, int level);
 DepLevel dep_level(const Problem &P, const HostLevel &L, const int32_t *bmap);
 amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,
                            const double *q, int64_t n, bool copy, const void **xs, const void **ys,
