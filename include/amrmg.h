@@ -276,7 +276,8 @@ amrmg_status amrmg_solve_noalloc(amrmg_ctx *ctx, double *const *rho, double *con
 /* Interpolate E to particles with the deposit's CIC weights, on the finest
  * level whose boxes hold all 8 stencil cells.  Ex, Ey, Ez device [n];
  * particles outside the domain get 0.  When n equals the particle count of
- * the last build, its spatial visiting order is used (the arrays are taken
+ * the last build and is at least 65536, its spatial visiting order is used
+ * (the arrays are taken
  * to hold the same particles, perhaps moved): E is computed in that order
  * into a staging buffer of 32 n bytes, which the context allocates on first
  * use and keeps, and then written in the caller's order; when the buffer

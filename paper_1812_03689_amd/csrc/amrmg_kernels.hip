@@ -1805,29 +1805,6 @@ __device__ __forceinline__ int64_t user_index(const DepLevel &D, const int64_t *
     return ubase[g] + (i & 7) + (int64_t)s.x * (j & 7) + (int64_t)s.y * (k & 7);
 }
 
-// Corners of a CIC stencil: bit d of c selects the upper cell along axis d;
-// st[d]: the stencil crosses a brick face along d.  A corner is "fresh"
-// when every upper axis of it crosses, so that its brick differs from the
-// bricks of the corners below it; spread_corners copies the value of each
-// fresh corner to the corners in the same brick (the bits of axes without a
-// crossing cleared), with fixed indices only.
-__device__ __forceinline__ bool corner_fresh(int c, const bool *st)
-{
-    return (!(c & 1) || st[0]) && (!(c & 2) || st[1]) && (!(c & 4) || st[2]);
-}
-
-template <class V>
-__device__ __forceinline__ void spread_corners(const bool *st, V *v)
-{
-    v[1] = st[0] ? v[1] : v[0];
-    v[2] = st[1] ? v[2] : v[0];
-    v[3] = st[1] ? (st[0] ? v[3] : v[2]) : v[1];
-    v[4] = st[2] ? v[4] : v[0];
-    v[5] = st[2] ? (st[0] ? v[5] : v[4]) : v[1];
-    v[6] = st[2] ? (st[1] ? v[6] : v[4]) : v[2];
-    v[7] = st[2] ? (st[1] ? (st[0] ? v[7] : v[6]) : v[5]) : v[3];
-}
-
 // Deposit every particle on every listed level.  A workgroup takes NT
 // consecutive particles of the visiting order (spatially sorted, so they are
 // close together) and, per level, accumulates their CIC weights in an LDS
@@ -2122,110 +2099,268 @@ __global__ void __launch_bounds__(256) k_pack_records(int64_t n, const P *x, con
 typedef double dpair __attribute__((ext_vector_type(2)));
 typedef dpair dpair_a8 __attribute__((aligned(8)));
 
+// Corners of a CIC stencil: bit d of c selects the upper cell along axis d;
+// st[d]: the stencil crosses a brick face along d.  A corner is "fresh"
+// when every upper axis of it crosses, so that its brick differs from the
+// bricks of the corners below it; spread_corners copies the value of each
+// fresh corner to the corners in the same brick (the bits of axes without a
+// crossing cleared), with fixed indices only.
+__device__ __forceinline__ bool corner_fresh(int c, const bool *st)
+{
+    return (!(c & 1) || st[0]) && (!(c & 2) || st[1]) && (!(c & 4) || st[2]);
+}
+
+template <class V>
+__device__ __forceinline__ void spread_corners(const bool *st, V *v)
+{
+    v[1] = st[0] ? v[1] : v[0];
+    v[2] = st[1] ? v[2] : v[0];
+    v[3] = st[1] ? (st[0] ? v[3] : v[2]) : v[1];
+    v[4] = st[2] ? v[4] : v[0];
+    v[5] = st[2] ? (st[0] ? v[5] : v[4]) : v[1];
+    v[6] = st[2] ? (st[1] ? v[6] : v[4]) : v[2];
+    v[7] = st[2] ? (st[1] ? (st[0] ? v[7] : v[6]) : v[5]) : v[3];
+}
+
+// E of one stencil from the caller's arrays E of a level, added to e when all
+// its 8 cells are on the level (else false).  Boxes are unions of whole
+// bricks, so the cells lie in at most two bricks per axis, each of which is
+// looked up once (mostly one in all).  The two x cells of a stencil row are
+// read together, also across a brick face (a box stores its rows whole);
+// where they are apart, at the face of a box, a lane reads the upper cell by
+// itself.  FEW: the rows one after another and every corner's brick looked
+// up, in fewer registers.
+template <bool FEW>
+__device__ __forceinline__ bool gather_cells(const DepLevel &D, const double *const *E, const int64_t *ubase,
+                                             const int2 *ustr, const int *i0, const int *i1, const double *f,
+                                             double (&e)[3])
+{
+    // st[d]: the stencil crosses a brick face along d
+    const int bstride[3] = {1, D.nbk[0], D.nbk[0] * D.nbk[1]};
+    bool st[3];
+    int base = 0, off[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        base += (i0[d] >> 3) * bstride[d];
+        st[d] = (i1[d] >> 3) != (i0[d] >> 3);
+        off[d] = st[d] ? bstride[d] : 0;
+    }
+    int g[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        g[c] = -1;
+        if (FEW || corner_fresh(c, st))
+            g[c] = D.bmap[base + ((c & 1) ? off[0] : 0) + ((c & 2) ? off[1] : 0) + ((c & 4) ? off[2] : 0)];
+    }
+    if (!FEW) spread_corners(st, g);
+    bool ok = true;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) ok = ok && g[c] >= 0;
+    if (!ok) return false;
+    // rows R at a time: their bases, then the pairs, then the upper cells
+    // that lie apart, each step's loads in flight together
+    constexpr int R = FEW ? 1 : 4;
+#pragma unroll 1
+    for (int r0 = 0; r0 < 4; r0 += R) {
+        int64_t u0[R], u1[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int r = r0 + q, j = (r & 1) ? i1[1] : i0[1], k = (r & 2) ? i1[2] : i0[2];
+            const int h = r == 0 ? g[0] : r == 1 ? g[2] : r == 2 ? g[4] : g[6];
+            const int2 s = ustr[h];
+            u0[q] = ubase[h] + (i0[0] & 7) + (int64_t)s.x * (j & 7) + (int64_t)s.y * (k & 7);
+            u1[q] = u0[q] + (i1[0] - i0[0]);
+        }
+        if (st[0])
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int r = r0 + q, j = (r & 1) ? i1[1] : i0[1], k = (r & 2) ? i1[2] : i0[2];
+                const int h = r == 0 ? g[1] : r == 1 ? g[3] : r == 2 ? g[5] : g[7];
+                const int2 s = ustr[h];
+                u1[q] = ubase[h] + (i1[0] & 7) + (int64_t)s.x * (j & 7) + (int64_t)s.y * (k & 7);
+            }
+        // the pair from the lower cell, or, where the upper is elsewhere, the
+        // pair that ends with the lower one (it may be the level's last)
+        double lo[R][3], hi[R][3];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int back = u1[q] != u0[q] + 1 && u0[q] > 0 ? 1 : 0;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                const dpair t = *(const dpair_a8 *)(E[d] + (u0[q] - back));
+                lo[q][d] = back ? t.y : t.x;
+                hi[q][d] = t.y;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+            if (u1[q] != u0[q] + 1)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) hi[q][d] = E[d][u1[q]];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int r = r0 + q;
+            const double wy = (r & 1) ? f[1] : 1.0 - f[1], wz = (r & 2) ? f[2] : 1.0 - f[2];
+            const double w0 = (1.0 - f[0]) * wy * wz, w1 = f[0] * wy * wz;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                e[d] += w0 * lo[q][d];
+                e[d] += w1 * hi[q][d];
+            }
+        }
+    }
+    return true;
+}
+
+// order the LDS accesses of a wavefront among its lanes
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// cells and bricks of a gather's field tile (one per wavefront)
+constexpr int GA_TILE = 256, GA_BRICKS = 32;
+
 // E at every particle from the finest level whose boxes hold all 8 cells of
 // its CIC stencil; particles are visited in the given (spatially sorted)
-// order so that neighbouring threads read neighbouring field cells.  ORD:
-// the positions are already in that order (x[i] is particle perm[i]), so
-// only the writes go through perm, or, with rec, E goes to rec[i] in the
-// visiting order for k_unpermute.  Boxes are unions of whole bricks, so the
-// stencil's 8 cells lie in at most two bricks per axis: each distinct brick
-// is looked up once (mostly one brick in all), and when the two x cells of
-// the stencil share a brick row they are read together.  Same sums in the
-// same order as cell by cell.
-template <class P, bool ORD>
-__global__ void __launch_bounds__(256) k_gather(int64_t n, const P *x, const P *y, const P *z, const uint32_t *perm,
-                                                GatherArgs G, const int64_t *ubase, const int2 *ustr, double *Ex,
-                                                double *Ey, double *Ez, double4 *rec)
+// order so that neighbouring threads read neighbouring field cells.  SRC: the
+// positions come as arrays (0, read through perm when it is given), as arrays
+// already in the order (1, x[i] is particle perm[i]) or as records in their
+// own order (2, read through perm).  E goes to its place directly or, with
+// out, to out[i] in the visiting order for k_unpermute.  Same sums in the
+// same order whichever way the cells are read.
+//
+// Read cell by cell it is bound by the vector cache, which returns a
+// wavefront's scattered 16-byte loads one or a few lanes at a time (its
+// data path 94 % busy on 9e6 particles of 128^3 + 2 levels, 380 us).  TILE:
+// where particles are dense, a wavefront loads the box of its stencils into
+// LDS once, whole rows at a time, and its lanes read their cells there (250
+// us; 4e6 moved particles on 96^3 + 2 levels 280 -> 165 us with the records).
+// A box larger than the tile is read cell by cell, in few registers, so that
+// the others keep five wavefronts a SIMD.
+template <class P, int SRC, bool TILE>
+__global__ void __launch_bounds__(256) k_gather(int64_t n, const P *x, const P *y, const P *z, const double4 *rec,
+                                                const uint32_t *perm, GatherArgs G, const int64_t *ubase,
+                                                const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out)
 {
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    int64_t p = perm ? (int64_t)perm[i] : i;
-    int64_t s = ORD ? i : p;
-    double X = (double)x[s], Y = (double)y[s], Z = (double)z[s];
-    double e[3] = {0.0, 0.0, 0.0};
-    for (int l = G.nlev - 1; l >= 0; --l) {
-        const DepLevel &D = G.lev[l];
-        int i0[3], i1[3];
-        double f[3];
-        if (!cic_stencil<P>(D, X, Y, Z, i0, i1, f)) break;
-        // st[d]: the stencil crosses a brick face along d
-        const int bstride[3] = {1, D.nbk[0], D.nbk[0] * D.nbk[1]};
-        bool st[3];
-        int base = 0, off[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            base += (i0[d] >> 3) * bstride[d];
-            st[d] = (i1[d] >> 3) != (i0[d] >> 3);
-            off[d] = st[d] ? bstride[d] : 0;
-        }
-        // brick of corner c (bit d of c: the upper cell along d), looked up
-        // for the corners whose upper axes all cross a brick face; every
-        // other corner shares the brick of one of those
-        int g[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            g[c] = -1;
-            if (corner_fresh(c, st))
-                g[c] = D.bmap[base + ((c & 1) ? off[0] : 0) + ((c & 2) ? off[1] : 0) + ((c & 4) ? off[2] : 0)];
-        }
-        spread_corners(st, g);
-        bool ok = true;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) ok = ok && g[c] >= 0;
-        if (!ok) continue;
-        int64_t u[8];
-        {
-            int64_t ub[8];
-            int usx[8], usy[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                ub[c] = 0;
-                usx[c] = usy[c] = 0;
-                if (corner_fresh(c, st)) {
-                    ub[c] = ubase[g[c]];
-                    const int2 t = ustr[g[c]];
-                    usx[c] = t.x;
-                    usy[c] = t.y;
-                }
-            }
-            spread_corners(st, ub);
-            spread_corners(st, usx);
-            spread_corners(st, usy);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const int ci = (c & 1) ? i1[0] : i0[0], cj = (c & 2) ? i1[1] : i0[1], ck = (c & 4) ? i1[2] : i0[2];
-                u[c] = ub[c] + (ci & 7) + (int64_t)usx[c] * (cj & 7) + (int64_t)usy[c] * (ck & 7);
-            }
-        }
-        // the field values of the 8 cells, x pairs with one load each when
-        // the upper x cell follows the lower one in the same brick row
-        double v[3][8];
-        if (!st[0] && i1[0] == i0[0] + 1) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-#pragma unroll
-                for (int c = 0; c < 8; c += 2) {
-                    const dpair t = *(const dpair_a8 *)(G.E[3 * l + d] + u[c]);
-                    v[d][c] = t.x;
-                    v[d][c + 1] = t.y;
-                }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool valid = i < n;
+    int64_t p = i;
+    double X = 0.0, Y = 0.0, Z = 0.0;
+    if (valid) {
+        if (perm) p = (int64_t)perm[i];
+        if (SRC == 2) {
+            const double4 r = rec[p];
+            X = r.x, Y = r.y, Z = r.z;
         } else {
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) v[d][c] = G.E[3 * l + d][u[c]];
+            const int64_t s = SRC == 1 ? i : p;
+            X = (double)x[s], Y = (double)y[s], Z = (double)z[s];
         }
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            double w = ((c & 1) ? f[0] : 1.0 - f[0]) * ((c & 2) ? f[1] : 1.0 - f[1]) *
-                       ((c & 4) ? f[2] : 1.0 - f[2]);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) e[d] += w * v[d][c];
-        }
-        break;
     }
-    if (rec) {
-        rec[i] = make_double4(e[0], e[1], e[2], 0.0);
+    double e[3] = {0.0, 0.0, 0.0};
+    bool pend = valid;
+    if (!TILE) {
+        for (int l = G.nlev - 1; l >= 0 && pend; --l) {
+            int i0[3], i1[3];
+            double f[3];
+            // (outside the domain: on every level)
+            pend = cic_stencil<P>(G.lev[l], X, Y, Z, i0, i1, f) &&
+                   !gather_cells<false>(G.lev[l], G.E + 3 * l, ubase, ustr, i0, i1, f, e);
+        }
+    } else {
+        __shared__ double field[4][3 * GA_TILE];
+        __shared__ int64_t tub[4][GA_BRICKS];
+        __shared__ int2 tus[4][GA_BRICKS];
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        double *wf = field[wave];
+        int64_t *wub = tub[wave];
+        int2 *wus = tus[wave];
+        for (int l = G.nlev - 1; l >= 0; --l) {
+            const DepLevel &D = G.lev[l];
+            int i0[3], i1[3];
+            double f[3];
+            pend = pend && cic_stencil<P>(D, X, Y, Z, i0, i1, f);
+            int wv[6];
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                wv[d] = wave_min(pend ? i0[d] : INT_MAX);
+                wv[3 + d] = wave_min(pend ? ~i1[d] : INT_MAX);
+            }
+            DepBox B;
+            B.set(wv);
+            if (B.empty()) break;  // every particle of the wavefront done
+            if (B.vol > GA_TILE || B.nbt > GA_BRICKS) {
+                if (pend) pend = !gather_cells<true>(D, G.E + 3 * l, ubase, ustr, i0, i1, f, e);
+                continue;
+            }
+            int64_t ub = -1;
+            int2 us = make_int2(0, 0);
+            if (lane < B.nbt) {
+                B.brick(D, ubase, ustr, lane, ub, us);
+                wub[lane] = ub;
+                wus[lane] = us;
+            }
+            const uint64_t there = __ballot(ub >= 0);
+            wave_fence();
+            bool ok = pend && there;
+            if (there != ((uint64_t)1 << B.nbt) - 1) {  // some brick of the box is not on the level
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const int bx = ((c & 1) ? i1[0] : i0[0]) >> 3, by = ((c & 2) ? i1[1] : i0[1]) >> 3,
+                              bz = ((c & 4) ? i1[2] : i0[2]) >> 3;
+                    if (ok) ok = (there >> ((bx - B.bx0) + B.nbx * ((by - B.by0) + B.nby * (bz - B.bz0)))) & 1;
+                }
+            }
+            if (!__ballot(ok)) continue;
+            // the box of the field into LDS, all loads in flight; quotients by
+            // its extents as in the deposit's flush
+            const float rex = 1.0f / (float)B.ex, rey = 1.0f / (float)B.ey;
+            double v[GA_TILE / 64][3];
+#pragma unroll
+            for (int j = 0; j < GA_TILE / 64; ++j) {
+                const int t = lane + 64 * j;
+                v[j][0] = v[j][1] = v[j][2] = 0.0;
+                if (t < (int)B.vol) {
+                    const int r = (int)(((float)t + 0.5f) * rex), rz = (int)(((float)r + 0.5f) * rey);
+                    const int ii = B.lo[0] + (t - r * B.ex), jj = B.lo[1] + (r - rz * B.ey), kk = B.lo[2] + rz;
+                    const int k = ((ii >> 3) - B.bx0) + B.nbx * (((jj >> 3) - B.by0) + B.nby * ((kk >> 3) - B.bz0));
+                    const int64_t u0 = wub[k];
+                    const int2 st = wus[k];
+                    if (u0 >= 0) {
+                        const int64_t u = u0 + (ii & 7) + (int64_t)st.x * (jj & 7) + (int64_t)st.y * (kk & 7);
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) v[j][d] = G.E[3 * l + d][u];
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < GA_TILE / 64; ++j)
+#pragma unroll
+                for (int d = 0; d < 3; ++d) wf[d * GA_TILE + lane + 64 * j] = v[j][d];
+            wave_fence();
+            if (ok) {
+                const int dx = i1[0] - i0[0], dy = B.ex * (i1[1] - i0[1]), dz = B.ex * B.ey * (i1[2] - i0[2]);
+                const double *c0 = wf + (i0[0] - B.lo[0]) + B.ex * ((i0[1] - B.lo[1]) + B.ey * (i0[2] - B.lo[2]));
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double *c = c0 + ((r & 1) ? dy : 0) + ((r & 2) ? dz : 0);
+                    const double wy = (r & 1) ? f[1] : 1.0 - f[1], wz = (r & 2) ? f[2] : 1.0 - f[2];
+                    const double w0 = (1.0 - f[0]) * wy * wz, w1 = f[0] * wy * wz;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        e[d] += w0 * c[d * GA_TILE];
+                        e[d] += w1 * c[d * GA_TILE + dx];
+                    }
+                }
+                pend = false;
+            }
+            wave_fence();
+        }
+    }
+    if (!valid) return;
+    if (out) {
+        out[i] = make_double4(e[0], e[1], e[2], 0.0);
         return;
     }
     Ex[p] = e[0];
@@ -2526,33 +2661,41 @@ void launch_pack_records(hipStream_t st, int pos_f32, int64_t n, const void *x, 
                      (const double *)z, q, rec);
 }
 
-template <class P, bool ORD>
-static void launch_gather_t(hipStream_t st, unsigned g, int64_t n, const void *x, const void *y, const void *z,
-                            const uint32_t *perm, const GatherArgs &G, const int64_t *ubase, const int2 *ustr,
-                            double *Ex, double *Ey, double *Ez, double4 *rec)
+template <class P, int SRC>
+static void launch_gather_t(hipStream_t st, int64_t n, const void *x, const void *y, const void *z,
+                            const double4 *rec, const uint32_t *perm, const GatherArgs &G, const int64_t *ubase,
+                            const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out, bool tile)
 {
-    AMRMG_LAUNCH((k_gather<P, ORD>), dim3(g), dim3(256), 0, st, n, (const P *)x, (const P *)y, (const P *)z, perm, G,
-                 ubase, ustr, Ex, Ey, Ez, rec);
+    const dim3 g(blocks_for(n, 256)), blk(256);
+    if (tile)
+        AMRMG_LAUNCH((k_gather<P, SRC, true>), g, blk, 0, st, n, (const P *)x, (const P *)y, (const P *)z, rec, perm,
+                     G, ubase, ustr, Ex, Ey, Ez, out);
+    else
+        AMRMG_LAUNCH((k_gather<P, SRC, false>), g, blk, 0, st, n, (const P *)x, (const P *)y, (const P *)z, rec, perm,
+                     G, ubase, ustr, Ex, Ey, Ez, out);
 }
 
 void launch_gather(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                   const uint32_t *perm, const uint32_t *iperm, const GatherArgs &G, const int64_t *ubase,
-                   const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *rec, bool ordered)
+                   const double4 *rec, const uint32_t *perm, const uint32_t *iperm, const GatherArgs &G,
+                   const int64_t *ubase, const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out,
+                   bool ordered, bool tile)
 {
     if (n <= 0) return;
-    unsigned g = blocks_for(n, 256);
-    if (!perm || !iperm) rec = nullptr;
+    if (!perm || !iperm) out = nullptr;
+    if (!perm) tile = false;
     if (ordered && perm) {
         if (pos_f32)
-            launch_gather_t<float, true>(st, g, n, x, y, z, perm, G, ubase, ustr, Ex, Ey, Ez, rec);
+            launch_gather_t<float, 1>(st, n, x, y, z, nullptr, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
         else
-            launch_gather_t<double, true>(st, g, n, x, y, z, perm, G, ubase, ustr, Ex, Ey, Ez, rec);
+            launch_gather_t<double, 1>(st, n, x, y, z, nullptr, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
+    } else if (rec && perm) {
+        launch_gather_t<double, 2>(st, n, nullptr, nullptr, nullptr, rec, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
     } else if (pos_f32) {
-        launch_gather_t<float, false>(st, g, n, x, y, z, perm, G, ubase, ustr, Ex, Ey, Ez, rec);
+        launch_gather_t<float, 0>(st, n, x, y, z, nullptr, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
     } else {
-        launch_gather_t<double, false>(st, g, n, x, y, z, perm, G, ubase, ustr, Ex, Ey, Ez, rec);
+        launch_gather_t<double, 0>(st, n, x, y, z, nullptr, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
     }
-    if (rec) AMRMG_LAUNCH(k_unpermute, dim3(g), dim3(256), 0, st, n, iperm, rec, Ex, Ey, Ez);
+    if (out) AMRMG_LAUNCH(k_unpermute, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, iperm, out, Ex, Ey, Ez);
 }
 
 void launch_tag(hipStream_t st, const double *v, int64_t n, double lambda, double *scratch, uint8_t *tags)

@@ -192,12 +192,16 @@ void launch_pack_records(hipStream_t st, int pos_f32, int64_t n, const void *x, 
 void launch_zero_levels(hipStream_t st, const DepArgs &A);
 // ordered: x, y, z are already in the order perm gives (x[i] is particle
 // perm[i], the build's ordered copy); E is written at perm[i].  With perm,
-// its inverse iperm and rec ([n] staging records), E goes to rec in the
+// its inverse iperm and out ([n] staging records), E goes to out in the
 // visiting order first and then to the caller's order by a second pass that
-// reads rec through iperm (coalesced writes instead of scattered ones).
+// reads out through iperm (coalesced writes instead of scattered ones).
+// rec: the positions as records in their own order, read through perm instead
+// of the arrays, or nullptr.  tile: the field through LDS, for dense
+// particles (with perm).
 void launch_gather(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
-                   const uint32_t *perm, const uint32_t *iperm, const GatherArgs &G, const int64_t *ubase,
-                   const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *rec, bool ordered = false);
+                   const double4 *rec, const uint32_t *perm, const uint32_t *iperm, const GatherArgs &G,
+                   const int64_t *ubase, const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out,
+                   bool ordered = false, bool tile = false);
 void launch_tag(hipStream_t st, const double *v, int64_t n, double lambda, double *scratch, uint8_t *tags);
 void launch_fill(hipStream_t st, double *v, int64_t n, double val);
 // spatial visiting order of the particles (stable radix sort by the

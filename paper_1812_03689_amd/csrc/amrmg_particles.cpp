@@ -251,6 +251,23 @@ static double4 *gather_records(amrmg_ctx *ctx, int64_t n)
     return (double4 *)ctx->gather_rec.p;
 }
 
+// A gather takes the field through LDS where particles are dense: at least
+// two per cell of the finest level, in enough wavefronts to hide the longer
+// chain (9e6 and 4e6 particles at about four per cell 341 -> 250 and 190 ->
+// 165 us; 1e6 at 0.8 per cell 45 -> 43; at less, or with 3e5, it loses: 1e7
+// 471 -> 478, 1.1e7 606 -> 688, 3e5 26 -> 33 us).
+static bool dense_gather(const amrmg_ctx *ctx, int64_t n)
+{
+    const Problem &pr = ctx->prob;
+    return n >= ((int64_t)1 << 19) && n >= 2 * pr.lev[pr.kg + pr.namr() - 1].ncells();
+}
+
+// A gather of fewer particles than this visits them in the caller's order
+// (the field is in the caches anyway) and writes E at its place, one launch:
+// 5e4 particles on 32^3 + 1 levels 10.1 -> 8.7 us, on 64^3 + 2 14.4 -> 14.6;
+// 1e5 14.0 -> 11.6 and 19.0 -> 19.5; 2e5 on 64^3 + 2 24.8 -> 30.3.
+constexpr int64_t kOrderMin = (int64_t)1 << 16;
+
 extern "C" amrmg_status amrmg_gather(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,
                                      int64_t n, double *const *E, double *Ex, double *Ey, double *Ez)
 {
@@ -260,11 +277,13 @@ extern "C" amrmg_status amrmg_gather(amrmg_ctx *ctx, int pos_dtype, const void *
     if (!E || n < 0 || (n > 0 && (!x || !y || !z || !Ex || !Ey || !Ez))) return fail(AMRMG_E_INVALID, "bad arguments");
     GatherArgs G;
     ST_TRY(gather_args(ctx, E, G));
-    const bool ord = ctx->perm_n == n;
-    double4 *rec = ord ? gather_records(ctx, n) : nullptr;
+    const bool ord = ctx->perm_n == n && n >= kOrderMin;
+    double4 *out = ord ? gather_records(ctx, n) : nullptr;
+    const double4 *rec = out ? moved_records(ctx, pos_dtype, x, y, z, nullptr, n) : nullptr;
     ctx->prof.begin(AMRMG_K_GATHER);
-    launch_gather(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, ord ? ctx->perm : nullptr,
-                  ord ? ctx->iperm : nullptr, G, ctx->ds.M.ubase, ctx->ds.M.ustr, Ex, Ey, Ez, rec);
+    launch_gather(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, rec, ord ? ctx->perm : nullptr,
+                  ord ? ctx->iperm : nullptr, G, ctx->ds.M.ubase, ctx->ds.M.ustr, Ex, Ey, Ez, out, false,
+                  dense_gather(ctx, n));
     ctx->prof.end(AMRMG_K_GATHER, (double)n * (3.0 * (pos_dtype == AMRMG_POS_F32 ? 4 : 8) + 24.0));
     HIP_TRY(hipGetLastError());
     return AMRMG_OK;
@@ -285,10 +304,10 @@ extern "C" amrmg_status amrmg_gather_built(amrmg_ctx *ctx, double *const *E, dou
     const char *base = (const char *)ctx->sorted.p;
     const char *xs = base + align256((size_t)n * 8), *ys = xs + align256((size_t)n * ps),
                *zs = ys + align256((size_t)n * ps);
-    double4 *rec = gather_records(ctx, n);
+    double4 *out = n >= kOrderMin ? gather_records(ctx, n) : nullptr;
     ctx->prof.begin(AMRMG_K_GATHER);
-    launch_gather(ctx->st, pos == AMRMG_POS_F32, n, xs, ys, zs, ctx->perm, ctx->iperm, G, ctx->ds.M.ubase,
-                  ctx->ds.M.ustr, Ex, Ey, Ez, rec, true);
+    launch_gather(ctx->st, pos == AMRMG_POS_F32, n, xs, ys, zs, nullptr, ctx->perm, ctx->iperm, G, ctx->ds.M.ubase,
+                  ctx->ds.M.ustr, Ex, Ey, Ez, out, true, dense_gather(ctx, n));
     ctx->prof.end(AMRMG_K_GATHER, (double)n * (3.0 * ps + 4.0 + 24.0));
     HIP_TRY(hipGetLastError());
     return AMRMG_OK;
