@@ -49,8 +49,9 @@ static const std::vector<double> &cached_direct_tables(const int n[3], const dou
 
 // the direct_tables layout with every matrix zero-padded to P x P, P = n
 // rounded up to a multiple of 16 (the matrix-core tile), and stored in the
-// order the matrix cores take it: for row block rb and step s, 64 values,
-// value l = M[16 rb + l % 16][4 s + l / 16]; eigenvalues as they are
+// order the matrix cores take it: for row block rb and chunk c of 16 columns
+// 64 x 4 values, lane l's four M[16 rb + l % 16][16 c + 4 (l / 16) ..]
+// together; eigenvalues as they are
 static void append_padded_tables(std::vector<double> &out, const int n[3], const std::vector<double> &t)
 {
     size_t off = 0;
@@ -60,11 +61,11 @@ static void append_padded_tables(std::vector<double> &out, const int n[3], const
             const size_t base = out.size();
             out.resize(base + (size_t)P * P, 0.0);
             for (int rb = 0; rb < P / 16; ++rb)
-                for (int s = 0; s < P / 4; ++s)
-                    for (int l = 0; l < 64; ++l) {
-                        const int a = 16 * rb + l % 16, b = 4 * s + l / 16;
+                for (int c = 0; c < P / 16; ++c)
+                    for (int i = 0; i < 256; ++i) {
+                        const int l = i >> 2, a = 16 * rb + l % 16, b = 16 * c + 4 * (l / 16) + i % 4;
                         if (a < N && b < N)
-                            out[base + ((size_t)rb * (P / 4) + s) * 64 + l] = t[off + (size_t)a * N + b];
+                            out[base + ((size_t)rb * (P / 16) + c) * 256 + i] = t[off + (size_t)a * N + b];
                     }
         }
     }

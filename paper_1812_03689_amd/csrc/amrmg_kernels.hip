@@ -1471,58 +1471,82 @@ typedef double dbl4 __attribute__((ext_vector_type(4)));
 
 // Products on the FP64 matrix cores, one 16 x 16 output tile per wavefront:
 // C[r][k] = sum_i Tb[r][i] D[k][i] with the table Tb (K x K, zero-padded, in
-// global memory in operand order) and the data D (rows of K values in LDS,
-// row stride ld).  v_mfma_f64 16x16x4 takes Tb[r0 + l%16][i0 + l/16] and
-// D[k0 + l%16][i0 + l/16] from lane l and returns C[r0 + l/16 + 4j][k0 + l%16]
-// in element j, so consecutive lanes hold consecutive k.
-// The wavefronts of a workgroup take the (R/16) x (N/16) output tiles in
-// turn; the K columns go in chunks of 64 (16 matrix-core steps, two
-// accumulation chains).  A wavefront can take its first tile's first chunk
-// of table rows early (dst_pre), so that those loads overlap the data loads.
-struct DPre {
-    double tb[16];
+// global memory in operand order) and the data D (K values per row).
+// v_mfma_f64 16x16x4 takes Tb[r0 + l%16][i] and D[k0 + l%16][i] from lane l,
+// each quarter of the wavefront (l/16) its own i, and returns C[r0 + l/16 +
+// 4j][k0 + l%16] in element j, so consecutive lanes hold consecutive k.  Which
+// i a step takes is free as long as both operands agree: quarter g takes the
+// four consecutive i = 16 c + 4 g + q in the four steps q of chunk c, so a
+// lane's operands of a chunk are one 32-byte piece of its row, of the table as
+// of the data, and the data come straight from global memory (a brick row, a
+// row of the scratch) without a detour through LDS.
+//
+// Bound by the latency of the chain launch, loads, 16 matrix steps (64^3), LDS,
+// 16 steps, stores, not by the matrix cores' rate.  With the data staged in
+// LDS first (two more barriers, one 87 KB workgroup a CU at 72 x 56 x 88) the
+// three launches took 31 us at 64^3, 68 at 72 x 56 x 88, 18 at 32^3 and 62 for
+// a batch of sixteen; now 19, 26, 10 and 38.
+// threads of the column transform: up to eight 16-row tiles go to as many
+// wavefronts (72 cells an axis 16.0 -> 13.2 us; the plane transforms, in more
+// workgroups than CUs, lose that way, 11.6 -> 14.4)
+constexpr int dst_threads(int NC) { return NC > 4 ? 512 : 256; }
+template <int NC>
+struct DOp {
+    double v[NC][4];
 };
-// this lane's operands of table rows r0.. for columns kc..kc+63:
-// tb[s] = Tb[r0 + l%16][kc + 4s + l/16], from the table stored in that order
-// (64 consecutive values per row block and step)
-__device__ __forceinline__ void dst_rows(const double *Tb, int K, int r0, int kc, double (&tb)[16])
+// this lane's operands of row block r0 of a table: chunk c, step q
+template <int NC>
+__device__ __forceinline__ void dst_rows(const double *Tb, int K, int r0, DOp<NC> &t)
 {
-    const double *p = Tb + ((size_t)(r0 >> 4) * (K >> 2) + (kc >> 2)) * 64 + (threadIdx.x & 63);
+    const double *p = Tb + (size_t)(r0 >> 4) * (K >> 4) * 256 + 4 * (threadIdx.x & 63);
 #pragma unroll
-    for (int s = 0; s < 16; ++s) tb[s] = kc + 4 * s < K ? p[64 * s] : 0.0;
-}
-__device__ __forceinline__ void dst_pre(const double *Tb, int R, int N, int K, DPre &pre)
-{
-    const int u = threadIdx.x >> 6, tr = R >> 4;
-    if (u < tr * (N >> 4)) dst_rows(Tb, K, (u % tr) << 4, 0, pre.tb);
-}
-template <class F>
-__device__ __forceinline__ void dst_product(const DPre &pre, const double *Tb, int R, int N, int K, const double *D,
-                                            int ld, F out)
-{
-    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, tr = R >> 4, tiles = tr * (N >> 4);
-    for (int u = wave; u < tiles; u += nw) {
-        const int r0 = (u % tr) << 4, k0 = (u / tr) << 4;
-        dbl4 a0 = {0.0, 0.0, 0.0, 0.0}, a1 = {0.0, 0.0, 0.0, 0.0};  // two chains (even and odd steps)
-        for (int kc = 0; kc < K; kc += 64) {
-            double tb[16];
-            if (u == wave && kc == 0) {
+    for (int c = 0; c < NC; ++c) {
+        if (16 * c < K)
 #pragma unroll
-                for (int q = 0; q < 16; ++q) tb[q] = pre.tb[q];
-            } else {
-                dst_rows(Tb, K, r0, kc, tb);
+            for (int h = 0; h < 2; ++h) {
+                const double2 a = *(const double2 *)(p + 256 * c + 2 * h);
+                t.v[c][2 * h] = a.x, t.v[c][2 * h + 1] = a.y;
             }
-            const double *d = D + (k0 + lr) * ld + lk + kc;
-#pragma unroll
-            for (int q = 0; q < 16; q += 2) {
-                if (kc + 4 * q < K) a0 = __builtin_amdgcn_mfma_f64_16x16x4f64(tb[q], d[4 * q], a0, 0, 0, 0);
-                if (kc + 4 * q + 4 < K) a1 = __builtin_amdgcn_mfma_f64_16x16x4f64(tb[q + 1], d[4 * q + 4], a1, 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) out(r0 + lk + 4 * j, k0 + lr, j, a0[j] + a1[j]);
     }
+}
+// rows of ld values in LDS: D[k0 + l%16][..]
+template <int NC>
+__device__ __forceinline__ void dst_lds(const double *D, int ld, int K, DOp<NC> &d)
+{
+    const double *p = D + (threadIdx.x & 15) * ld + 4 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (16 * c < K)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double2 a = *(const double2 *)(p + 16 * c + 2 * h);
+                d.v[c][2 * h] = a.x, d.v[c][2 * h + 1] = a.y;
+            }
+}
+template <int NC>
+__device__ __forceinline__ dbl4 dst_mfma(const DOp<NC> &t, const DOp<NC> &d, int K)
+{
+    dbl4 a0 = {0.0, 0.0, 0.0, 0.0}, a1 = {0.0, 0.0, 0.0, 0.0};  // two chains (even and odd steps)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        if (16 * c < K)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                a0 = __builtin_amdgcn_mfma_f64_16x16x4f64(t.v[c][q], d.v[c][q], a0, 0, 0, 0);
+                a1 = __builtin_amdgcn_mfma_f64_16x16x4f64(t.v[c][q + 1], d.v[c][q + 1], a1, 0, 0, 0);
+            }
+    return a0 + a1;
+}
+// four consecutive values of T as doubles
+__device__ __forceinline__ void load4(const float *p, double (&v)[4])
+{
+    const float4 a = *(const float4 *)p;
+    v[0] = (double)a.x, v[1] = (double)a.y, v[2] = (double)a.z, v[3] = (double)a.w;
+}
+__device__ __forceinline__ void load4(const double *p, double (&v)[4])
+{
+    const double2 a = *(const double2 *)p, b = *(const double2 *)(p + 2);
+    v[0] = a.x, v[1] = a.y, v[2] = b.x, v[3] = b.y;
 }
 
 // table pool layout per job: forward and inverse matrices of x, y, z, each
@@ -1543,13 +1567,14 @@ __device__ __forceinline__ const double *dst_table(const DirectJob &J, const dou
 // phi += e): the x transform of the whole plane restricted to the block,
 // then the y transform of the block.  planes[i] = (job, z | block << 8), or
 // with jobs == nullptr the one job J1 and workgroup z * blocks + block.
-// Dynamic LDS: rows + 16 rows of ld doubles, rows = pad16(largest edge).
-template <class T, bool INV>
+// NC: chunks of 16 of the longest edge.
+template <class T, bool INV, int NC>
 __global__ void __launch_bounds__(256) k_dst_plane(const DirectJob *jobs, const int2 *planes, DirectJob J1,
-                                                  const double *tab, double *W, const T *r, T *e, double *phib,
-                                                  int phi_update, int ld, int rows)
+                                                   const double *tab, double *W, const T *r, T *e, double *phib,
+                                                   int phi_update)
 {
-    extern __shared__ double sm[];
+    constexpr int LD = 16 * NC + 2;  // (16-byte rows whose starts fall in different banks)
+    __shared__ double Bt[16 * LD];   // x-transformed block [kx - kx0][y]
     // one job (jobs == nullptr): J1, workgroup = z * blocks + block; else from the lists
     int z, kb;
     DirectJob J;
@@ -1566,58 +1591,64 @@ __global__ void __launch_bounds__(256) k_dst_plane(const DirectJob *jobs, const 
     }
     const int nx = J.dn[0], ny = J.dn[1], kx0 = kb << 4, np = nx * ny;
     const int px = pad16(nx), py = pad16(ny);
-    double *A = sm, *Bt = sm + rows * ld;  // plane [y][x]; x-transformed block [kx - kx0][y]
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     double *w = W + J.w + (size_t)np * z;
-    // the x table's first rows first, then the plane: those loads in flight together
-    const double *Mx = dst_table(J, tab, 0, INV) + (size_t)(kx0 >> 4) * (px >> 2) * 64, *My = dst_table(J, tab, 1, INV);
-    DPre p1;
-    dst_pre(Mx, 16, py, px, p1);
-    // the plane in rows of 64: x = xb + thread % 64, y = yb + thread / 64 + 4 q
-    for (int xb = 0; xb < px; xb += 64)
-        for (int yb = 0; yb < py; yb += 64) {
-            const int x = xb + (threadIdx.x & 63), y0 = yb + (threadIdx.x >> 6);
-            double v[16];
+    const double *Mx = dst_table(J, tab, 0, INV), *My = dst_table(J, tab, 1, INV);
+    DOp<NC> tx, ty;
+    dst_rows<NC>(Mx, px, kx0, tx);
+    // along x: Bt[kx - kx0][y] = sum_x Mx[kx][x] plane[y][x], 16 rows y a tile
+    for (int y0 = wave << 4; y0 < py; y0 += 64) {
+        const int y = y0 + lr;
+        DOp<NC> d;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int y = y0 + 4 * q;
-                v[q] = 0.0;
-                if (y < ny && x < nx) v[q] = INV ? w[y * nx + x] : (double)r[direct_cell(J, x, y, z)];
-            }
+        for (int c = 0; c < NC; ++c) {
+            const int x = 16 * c + 4 * lk;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int y = y0 + 4 * q;
-                if (y < py && x < px) A[y * ld + x] = v[q];
+            for (int q = 0; q < 4; ++q) d.v[c][q] = 0.0;
+            if (y < ny && x < nx) {
+                if (INV) load4(w + y * nx + x, d.v[c]);
+                else load4(r + direct_cell(J, x, y, z), d.v[c]);
             }
         }
-    DPre p2;
-    dst_pre(My, py, 16, py, p2);
+        if (y0 == (wave << 4)) dst_rows<NC>(My, py, y0, ty);  // in flight with the plane
+        const dbl4 s = dst_mfma<NC>(tx, d, px);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) Bt[(lk + 4 * j) * LD + y] = s[j];
+    }
     __syncthreads();
-    // along x: Bt[kx - kx0][y] = sum_x Mx[kx][x] A[y][x]
-    dst_product(p1, Mx, 16, py, px, A, ld, [&](int kx, int y, int, double s) { Bt[kx * ld + y] = s; });
-    __syncthreads();
-    // along y: out[ky][kx] = sum_y My[ky][y] Bt[kx - kx0][y]
-    dst_product(p2, My, py, 16, py, Bt, ld, [&](int y, int xl, int, double s) {
-        const int x = kx0 + xl;
-        if (x >= nx || y >= ny) return;
-        if (!INV) {
-            w[y * nx + x] = s;
-        } else {
-            const size_t bi = direct_cell(J, x, y, z);
-            e[bi] = (T)s;
-            if (phi_update && J.amr) phib[bi] += s;
+    // along y: out[ky][kx] = sum_y My[ky][y] Bt[kx - kx0][y], 16 rows ky a tile
+    DOp<NC> d;
+    dst_lds<NC>(Bt, LD, py, d);
+    const int x = kx0 + lr;
+    for (int y0 = wave << 4; y0 < py; y0 += 64) {
+        if (y0 != (wave << 4)) dst_rows<NC>(My, py, y0, ty);
+        const dbl4 s = dst_mfma<NC>(ty, d, py);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int y = y0 + lk + 4 * j;
+            if (x >= nx || y >= ny) continue;
+            if (!INV) {
+                w[y * nx + x] = s[j];
+            } else {
+                const size_t bi = direct_cell(J, x, y, z);
+                e[bi] = (T)s[j];
+                if (phi_update && J.amr) phib[bi] += s[j];
+            }
         }
-    });
+    }
 }
 
-// transform along z of a group of DIRECT_COLS columns: forward, division by
-// the eigenvalue sum, inverse.  groups[i] = (job, first column), or with
-// jobs == nullptr the one job J1 and columns from DIRECT_COLS * workgroup.  Dynamic
-// LDS: two arrays of DIRECT_COLS rows of ld doubles.
-__global__ void __launch_bounds__(256) k_dst_column(const DirectJob *jobs, const int2 *groups, DirectJob J1,
-                                                   const double *tab, double *W, int ld)
+// transform along z of a group of DIRECT_COLS = 16 columns: forward, division
+// by the eigenvalue sum, inverse.  groups[i] = (job, first column), or with
+// jobs == nullptr the one job J1 and columns from DIRECT_COLS * workgroup.
+template <int NC>
+__global__ void __launch_bounds__(dst_threads(NC)) k_dst_column(const DirectJob *jobs, const int2 *groups, DirectJob J1,
+                                                    const double *tab, double *W)
 {
-    extern __shared__ double sm[];
-    double *A = sm, *C = sm + DIRECT_COLS * ld;  // [col][z], [col][kz]
+    static_assert(DIRECT_COLS == 16, "one matrix-core tile of columns");
+    constexpr int LD = 16 * NC + 2;
+    __shared__ double C[16 * LD];  // [column][kz]
     DirectJob J;
     int c0;  // np is a multiple of DIRECT_COLS
     if (!jobs) {  // one job: J1, workgroup = column group
@@ -1629,35 +1660,50 @@ __global__ void __launch_bounds__(256) k_dst_column(const DirectJob *jobs, const
         c0 = gr.y;
     }
     const int nx = J.dn[0], ny = J.dn[1], nz = J.dn[2], np = nx * ny, pz = pad16(nz);
+    const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double *mux = dst_table(J, tab, 2, false) + 2 * pz * pz, *muy = mux + nx, *muz = muy + ny;
     const double *Fz = dst_table(J, tab, 2, false), *Bz = dst_table(J, tab, 2, true);
-    double *w = W + J.w;
-    DPre pf;
-    dst_pre(Fz, pz, DIRECT_COLS, pz, pf);
-    constexpr int NV = DIRECT_DIM * DIRECT_COLS / 256;
-    double v[NV];
+    const int col = c0 + lr;
+    double *w = W + J.w + col;
+    DOp<NC> tf, tb, d;
+    // (a wavefront without a tile of its own loads nothing)
+    if ((wave << 4) < pz) {
+        dst_rows<NC>(Fz, pz, wave << 4, tf);
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        const int i = threadIdx.x + 256 * q, zz = i / DIRECT_COLS, c = i % DIRECT_COLS;
-        v[q] = zz < nz ? w[(size_t)np * zz + c0 + c] : 0.0;
-    }
+        for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        const int i = threadIdx.x + 256 * q, zz = i / DIRECT_COLS, c = i % DIRECT_COLS;
-        if (zz < pz) A[c * ld + zz] = v[q];
+            for (int q = 0; q < 4; ++q) {
+                const int zz = 16 * c + 4 * lk + q;
+                d.v[c][q] = zz < nz ? w[(size_t)np * zz] : 0.0;
+            }
+        dst_rows<NC>(Bz, pz, wave << 4, tb);
     }
-    DPre pb;
-    dst_pre(Bz, pz, DIRECT_COLS, pz, pb);
-    __syncthreads();
+    const double mxy = mux[col % nx] + muy[col / nx];
     // forward, then the division by the eigenvalue sum of (column, kz)
-    dst_product(pf, Fz, pz, DIRECT_COLS, pz, A, ld, [&](int kz, int c, int, double s) {
-        const int col = c0 + c;
-        C[c * ld + kz] = kz < nz ? s / (mux[col % nx] + muy[col / nx] + muz[kz]) : 0.0;
-    });
+    for (int z0 = wave << 4; z0 < pz; z0 += dst_threads(NC) / 4) {
+        double mz[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mz[j] = z0 + lk + 4 * j < nz ? muz[z0 + lk + 4 * j] : 1.0;
+        if (z0 != (wave << 4)) dst_rows<NC>(Fz, pz, z0, tf);
+        const dbl4 s = dst_mfma<NC>(tf, d, pz);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int kz = z0 + lk + 4 * j;
+            C[lr * LD + kz] = kz < nz ? s[j] / (mxy + mz[j]) : 0.0;
+        }
+    }
     __syncthreads();
-    dst_product(pb, Bz, pz, DIRECT_COLS, pz, C, ld, [&](int zz, int c, int, double s) {
-        if (zz < nz) w[(size_t)np * zz + c0 + c] = s;
-    });
+    dst_lds<NC>(C, LD, pz, d);
+    for (int z0 = wave << 4; z0 < pz; z0 += dst_threads(NC) / 4) {
+        if (z0 != (wave << 4)) dst_rows<NC>(Bz, pz, z0, tb);
+        const dbl4 s = dst_mfma<NC>(tb, d, pz);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int zz = z0 + lk + 4 * j;
+            if (zz < nz) w[(size_t)np * zz] = s[j];
+        }
+    }
 }
 
 // one workgroup per job: jobs[i] = (first brick, bricks, offset of its four
@@ -2762,23 +2808,23 @@ void launch_direct(hipStream_t st, const DirectJob *jobs, const int2 *planes, in
                    int maxdim, const DirectJob *one)
 {
     if (nplanes <= 0) return;
-    const int rows = (maxdim + 15) & ~15, ld = rows + 1;
-    const size_t sp = sizeof(double) * (rows + 16) * ld, sc = sizeof(double) * 2 * DIRECT_COLS * ld;
-    static bool attr = false;  // allow more than 64 KiB of dynamic LDS
-    if (!attr) {
-        const int lim = (int)(sizeof(double) * (DIRECT_DIM + 16) * (DIRECT_DIM + 1));
-        (void)hipFuncSetAttribute((const void *)k_dst_plane<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-        (void)hipFuncSetAttribute((const void *)k_dst_plane<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lim);
-        attr = true;
-    }
     // one job: its record goes by value and the workgroups' lists are not read
     const DirectJob J1 = one ? *one : DirectJob{};
     const DirectJob *jl = one ? nullptr : jobs;
-    AMRMG_LAUNCH((k_dst_plane<T, false>), dim3(nplanes), dim3(256), sp, st, jl, planes, J1, tab, W, r, e, phib,
-                 (int)phi_update, ld, rows);
-    AMRMG_LAUNCH(k_dst_column, dim3(ngroups), dim3(256), sc, st, jl, groups, J1, tab, W, ld);
-    AMRMG_LAUNCH((k_dst_plane<T, true>), dim3(nplanes), dim3(256), sp, st, jl, planes, J1, tab, W, r, e, phib,
-                 (int)phi_update, ld, rows);
+    const int pu = (int)phi_update;
+#define AMRMG_DIRECT(NC)                                                                                           \
+    do {                                                                                                           \
+        AMRMG_LAUNCH((k_dst_plane<T, false, NC>), dim3(nplanes), dim3(256), 0, st, jl, planes, J1, tab, W, r, e, phib, \
+                     pu);                                                                                          \
+        AMRMG_LAUNCH((k_dst_column<NC>), dim3(ngroups), dim3(dst_threads(NC)), 0, st, jl, groups, J1, tab, W);                 \
+        AMRMG_LAUNCH((k_dst_plane<T, true, NC>), dim3(nplanes), dim3(256), 0, st, jl, planes, J1, tab, W, r, e, phib,  \
+                     pu);                                                                                          \
+    } while (0)
+    // registers for the operands of the longest edge
+    if (maxdim <= 32) AMRMG_DIRECT(2);
+    else if (maxdim <= 64) AMRMG_DIRECT(4);
+    else AMRMG_DIRECT(DIRECT_DIM / 16);
+#undef AMRMG_DIRECT
 }
 
 template <class T>

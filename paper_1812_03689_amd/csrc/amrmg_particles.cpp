@@ -79,10 +79,15 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
         cz = cy + align256((size_t)n * ps);
     }
     uint32_t *perm = (uint32_t *)ctx->sort_vals.p;
-    if (ctx->rec_own.ensure(sizeof(double4) * (size_t)n) == hipSuccess)
-        ctx->rec = (double4 *)ctx->rec_own.p;
-    else
-        (void)hipGetLastError();
+    // records from 2.6e5 particles: fewer stay in the caches, where scattered
+    // reads are cheap, and need no buffer of their own
+    constexpr int64_t kRecMin = (int64_t)1 << 18;
+    if (n >= kRecMin) {
+        if (ctx->rec_own.ensure(sizeof(double4) * (size_t)n) == hipSuccess)
+            ctx->rec = (double4 *)ctx->rec_own.p;
+        else
+            (void)hipGetLastError();
+    }
     HIP_TRY(particle_order(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->rec, P.lo, P.hi, P.n0, P.max_level,
                            ctx->sort_scratch.p, ctx->sort_scratch.cap, perm, perm + n));
     ctx->perm = perm;
