@@ -164,18 +164,23 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         boundary_ghost(*probs[m.ent[i].prob], m.ent[i].h, lc[i].abnd);
         lc[i].amr = m.ent[i].amr;
     }
-    // norm ranges: every AMR level of every problem, entry order
-    static thread_local std::vector<int32_t> rg, jobs;
-    rg.clear();
+    // norm ranges: every AMR level of every problem, entry order, in pieces
+    static thread_local std::vector<int32_t> jobs, nfirst;
+    static thread_local std::vector<int4> npieces;
+    npieces.clear();
+    nfirst.assign(1, 0);
     D.range_prob.clear();
     D.range_amr.clear();
     for (const auto &e : m.ent)
         if (e.amr >= 0) {
-            rg.push_back(e.b0);
-            rg.push_back(e.nb);
+            for (int o = 0; o < e.nb; o += NORM_PIECE)
+                npieces.push_back(make_int4(e.b0 + o, std::min(NORM_PIECE, e.nb - o), (int)D.range_prob.size(), 0));
+            nfirst.push_back((int)npieces.size());
             D.range_prob.push_back(e.prob);
             D.range_amr.push_back(e.amr);
         }
+    D.norms.npiece = (int)npieces.size();
+    D.norms.n = (int)D.range_prob.size();
     // bottom solves: the coarsest level of each problem
     jobs.clear();
     size_t off = 0;
@@ -271,12 +276,14 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     if (groups.empty()) groups.push_back(make_int2(0, 0));
 
     Packer P;
-    int32_t *drg = nullptr, *dj = nullptr, *cfi = nullptr;
+    int32_t *dnf = nullptr, *dj = nullptr, *cfi = nullptr;
+    int4 *dnp = nullptr;
     uint8_t *cfp = nullptr;
     double *gbc = nullptr;
     LevelConst *dlc = nullptr;
     P.add(lc, &dlc);
-    P.add(rg, &drg);
+    P.add(npieces, &dnp);
+    P.add(nfirst, &dnf);
     P.add(jobs, &dj);
     P.add(cj, &D.d_cjobs);
     EntryDev *dent = nullptr;
@@ -401,7 +408,8 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.M.lc = dlc;
     D.M.nbc = m.nbc;
     D.M.ncf = m.ncf;
-    D.d_ranges = (int2 *)drg;
+    D.norms.pieces = dnp;
+    D.norms.first = dnf;
     D.d_jobs = (int4 *)dj;
     int32_t *dpool = B.pool;
     HIP_TRY(hipMemsetAsync(D.d_face_err, 0, sizeof(int), st));
@@ -421,8 +429,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.d_rho = D.d_phi + ne;
     D.d_rout = D.d_rho + ne;
     D.d_E = D.d_rout + ne;
-    HIP_TRY(D.h_normbuf.ensure(sizeof(double) * 2 * (D.range_prob.size() + 1)));
-    D.h_norm = (double *)D.h_normbuf.p;
     HIP_TRY(D.pubbuf.ensure(sizeof(double) * (4 * D.range_prob.size() + 8)));
     D.h_seq = (unsigned *)D.pubbuf.p;
     D.h_pub = (double *)D.pubbuf.p + 1;

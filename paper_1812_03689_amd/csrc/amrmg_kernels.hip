@@ -75,6 +75,28 @@ __device__ __forceinline__ void transverse(int d, int &du, int &dv)
     dv = (d == 2) ? 1 : 2;
 }
 
+// Two cells adjacent along x in one row of a box: one 16-byte access (8-byte
+// alignment is enough for a global access on CDNA).
+typedef double dpair __attribute__((ext_vector_type(2)));
+typedef dpair dpair_a8 __attribute__((aligned(8)));
+
+// a / h, correctly rounded, from rh = 1/h rounded to nearest: with the
+// remainder a - h (a rh) exact in one fma, the corrected quotient is the
+// rounded one (Markstein's theorem), in 3 instructions instead of the
+// division's dozen
+__device__ __forceinline__ double div_by(double a, double h, double rh)
+{
+    const double q = a * rh;
+    return fma(fma(-q, h, a), rh, q);
+}
+
+// order the LDS accesses of a wavefront among its lanes
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // accessors: value of local cell l of brick b
 // ---------------------------------------------------------------------------
@@ -182,7 +204,7 @@ __device__ double block_reduce(double v, int op)
 // coarse-fine face it holds bv of the ghost a*u_c + bv, and alpha[face] holds
 // a, stored as a - 2 on a boundary face so that its sign tells the kinds
 // apart (coarse-fine 2/3 > 0, same level 0, boundary a - 2 < -1 since
-// |a| < 1 or a = -1; tile_ab and ghost_shift take the 2 back).  All loads of
+// |a| < 1 or a = -1; tile_ab takes the 2 back).  All loads of
 // a tile are independent and issued before one barrier.
 // ---------------------------------------------------------------------------
 constexpr int TE = 10;
@@ -422,32 +444,29 @@ struct Row8<double> {
 // Composite residual r = rho/eps0 - A_comp phi on uncovered cells (zero on
 // covered ones) of a range or list of AMR bricks, from FP64 phi and rho in
 // brick layout, written as T in brick layout (r_out) and/or FP64 in the
-// caller's layout (r_user), with one partial norm per wavefront (part[2 b],
-// part[2 b + 1]).  A face towards a covered cell takes the mean of the four
-// fine fluxes through it (flux matching), from the fine sums ffs of phi.  Bricks with no covered cell and no
-// covered face neighbour (every brick of the finest level) take the plain
-// 7-point stencil on the tile, corrected on brick faces whose halo is a
-// boundary or coarse-fine ghost.  Two wavefronts per brick, one barrier.
-constexpr int RT = 128;
-
-// a u_c + bv - bv_halo for a ghost a u_c + bv whose halo slot holds bv_halo
-// (bv = bv_halo - u_in / 5 on a coarse-fine face), from the stored alpha
-// (a, or a - 2 on a boundary face)
-__device__ __forceinline__ double ghost_shift(double a, double uc, double uin)
-{
-    return a > 0.0 ? a * uc - 0.2 * uin : (a < 0.0 ? (a + 2.0) * uc : 0.0);
-}
+// caller's layout (r_user), with one partial norm per brick (part[b]).  A
+// face towards a covered cell takes the mean of the four fine fluxes through
+// it (flux matching), from the fine sums ffs of phi.
 
 // One wavefront per brick, lane (y, z) holding the x-row (y, z) of phi and
 // rho in registers and the rows of phi with the y and z halo rows in LDS, as
 // the sweep kernel does (rrow); the face kinds and the covered-octant masks
-// of the brick and of its face neighbours come through scalar loads.  Each lane writes its row of r and one partial norm per brick
-// (part[2 b]; part[2 b + 1] = 0).
-template <class T, bool ZERO, int BPW>
+// of the brick and of its face neighbours come through scalar loads.  Each
+// lane writes its row of r.  BOTH: also the partial norm of the residual of
+// phi = 0 (rho/eps0 and the Dirichlet data alone), in part[n_part + b].
+//
+// On small hierarchies it is bound by its chain of loads.  The fine sums next
+// to covered cells come by half rows (four consecutive sums of one child's
+// face); loaded cell
+// by cell and face by face, each waiting for its own, they made it 15.0 us on 64^3 + 2 levels (now
+// 12.3) and 8.5 on 32^3 + 1 (now 6.1).  A direction at a time, not all: on
+// large hierarchies it streams, and its registers must leave five wavefronts
+// a SIMD.
+template <class T, bool BOTH, int BPW>
 __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, int nb, const double *phib,
                                                              const double *rhob, double inv_eps0,
-                                                             const double *cp_phi, T *r_out, double *part, int norm_p,
-                                                             const int32_t *list, double *const *r_user,
+                                                             const double *cp_phi, T *r_out, double *part, int n_part,
+                                                             int norm_p, const int32_t *list, double *const *r_user,
                                                              const double *ffs)
 {
     __shared__ double rows_all[BPW][RW * RW * RS];
@@ -480,7 +499,7 @@ __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, 
     // the children of the brick and of its face neighbours, for the fine
     // sums of covered faces: kids[8 f + o] of face neighbour f, kids[48 + o]
     // of the brick (-1 where none); read after the barrier below
-    if (!ZERO && any_cov && !all_cov && lane < 56) {
+    if (any_cov && !all_cov && lane < 56) {
         const int nbl = lane < 48 ? M.nbr[b * 6 + (lane >> 3)] : b;
         kids[lane] = nbl >= 0 ? M.child[nbl * 8 + (lane & 7)] : -1;
     }
@@ -489,7 +508,7 @@ __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, 
     for (int i = 0; i < 8; ++i) rv[i] = u[i] = 0.0;
     if (!all_cov) {
         Row8<double>::load(rhob + rb, rv);
-        if (!ZERO) Row8<double>::load(phib + rb, u);
+        Row8<double>::load(phib + rb, u);
     }
     // halo slots: the neighbour's phi, 2 g on the boundary (the Dirichlet
     // data enter here), or the coarse part of the coarse-fine ghost
@@ -499,11 +518,11 @@ __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, 
         const int uu = lane & 7, vv = lane >> 3;
         if (kind[f] == 0) {
             const int c = d == 0 ? md + 8 * uu + 64 * vv : (d == 1 ? uu + 8 * md + 64 * vv : uu + 8 * vv + 64 * md);
-            hs[f] = ZERO ? 0.0 : phib[(size_t)nbf[f] * BRICK_CELLS + c];
+            hs[f] = phib[(size_t)nbf[f] * BRICK_CELLS + c];
         } else if (kind[f] == 1) {
             hs[f] = 2.0 * M.gbc[(size_t)(-1 - nbf[f]) * 64 + lane];
         } else {
-            hs[f] = (ZERO || !cp_phi) ? 0.0 : cp_phi[(size_t)(-1 - nbf[f] - M.nbc) * 64 + lane];
+            hs[f] = cp_phi[(size_t)(-1 - nbf[f] - M.nbc) * 64 + lane];
         }
     }
     const int rym = rrow(y - 1, z), ryp = rrow(y + 1, z), rzm = rrow(y, z - 1), rzp = rrow(y, z + 1), rme = rrow(y, z);
@@ -525,46 +544,98 @@ __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, 
     const double wxp0 = kind[0] == 2 ? 0.8 : 1.0, wxm7 = kind[1] == 2 ? 0.8 : 1.0;
     const double den = ih2y * (2.0 - aym - ayp) + ih2z * (2.0 - azm - azp) + 2.0 * ih2x;
     __syncthreads();
-    double r[8], acc = 0.0;
+    const int ozy = ((y >> 2) << 1) | ((z >> 2) << 2);  // the row's octants: ozy, ozy | 1
+    const bool cov[2] = {((cm >> ozy) & 1) != 0, ((cm >> (ozy | 1)) & 1) != 0};
+    double r[8], acc = 0.0, acc0 = 0.0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
-        r[x] = 0.0;
-        if (all_cov) continue;
         const double uc = u[x];
         const double xm = x == 0 ? hs[0] : u[x - 1], xp = x == 7 ? hs[1] : u[x + 1];
         const double wxm = x == 7 ? wxm7 : 1.0, wxp = x == 0 ? wxp0 : 1.0;
         const double dc = den - (x == 0 ? ih2x * ag[0] : 0.0) - (x == 7 ? ih2x * ag[1] : 0.0);
         const double ym = rows[rym + x], yp = rows[ryp + x], zm = rows[rzm + x], zp = rows[rzp + x];
-        double Au = dc * uc - (ih2x * (wxm * xm + wxp * xp) + ih2y * (wym * ym + wyp * yp) +
-                               ih2z * (wzm * zm + wzp * zp));
-        const int oc = (x >> 2) | ((y >> 2) << 1) | ((z >> 2) << 2);
-        const bool mine_cov = (cm >> oc) & 1;
-        if (any_cov && !mine_cov) {
-            // a face towards a covered cell of this level: the flux through
-            // it is the mean of the four fine fluxes (the fine sums), in
-            // place of the same-level term ih2 (u_c - u_nb)
+        r[x] = rv[x] * inv_eps0 - (dc * uc - (ih2x * (wxm * xm + wxp * xp) + ih2y * (wym * ym + wyp * yp) +
+                                              ih2z * (wzm * zm + wzp * zp)));
+        if (BOTH) {
+            // phi = 0: of the operator only the boundary data stay
+            double g = 0.0;
+            if (x == 0 && kind[0] == 1) g += ih2x * hs[0];
+            if (x == 7 && kind[1] == 1) g += ih2x * hs[1];
+            if (y == 0 && kind[2] == 1) g += ih2y * ym;
+            if (y == 7 && kind[3] == 1) g += ih2y * yp;
+            if (z == 0 && kind[4] == 1) g += ih2z * zm;
+            if (z == 7 && kind[5] == 1) g += ih2z * zp;
+            const double av = cov[x >> 2] ? 0.0 : fabs(rv[x] * inv_eps0 + g);
+            acc0 = norm_p == 2 ? acc0 + av * av : norm_p == 1 ? acc0 + av : fmax(acc0, av);
+        }
+    }
+    if (any_cov && !all_cov) {
+        // a face towards a covered cell of this level: the flux through it is
+        // the mean of the four fine fluxes (the fine sums), in place of the
+        // same-level term ih2 (u_c - u_nb).  Along y and z a whole half of the
+        // row (one octant) has the covered neighbour or has not.
+#pragma unroll 1
+        for (int f = 2; f < 6; ++f) {
+            const int d = f >> 1, s = f & 1, q = (d == 1 ? y : z) + (s ? 1 : -1), l = q & 7;
+            const double ih2 = d == 1 ? ih2y : ih2z;
+            const bool inside = q == l;
+            const int qo = d == 1 ? ((l >> 2) << 1) | ((z >> 2) << 2) : ((y >> 2) << 1) | ((l >> 2) << 2);
+            const uint32_t nm = inside ? cm : (f == 2 ? ncm[2] : f == 3 ? ncm[3] : f == 4 ? ncm[4] : ncm[5]);
+            const double *nrow = rows + (d == 1 ? (s ? ryp : rym) : (s ? rzp : rzm));
+            bool on[2];
+            double2 a[2], c[2];
 #pragma unroll
-            for (int f = 0; f < 6; ++f) {
-                const int d = f >> 1, sg = (f & 1) ? 1 : -1;
-                const int qx = x + (d == 0 ? sg : 0), qy = y + (d == 1 ? sg : 0), qz = z + (d == 2 ? sg : 0);
-                const bool inside = ((qx | qy | qz) & ~7) == 0;
-                if (!inside && kind[f] != 0) continue;
-                const int lx = qx & 7, ly = qy & 7, lz = qz & 7;
-                const int qo = (lx >> 2) | ((ly >> 2) << 1) | ((lz >> 2) << 2);
-                if (!(((inside ? cm : ncm[f]) >> qo) & 1)) continue;
-                const double unb = d == 0 ? (f & 1 ? xp : xm) : (d == 1 ? (f & 1 ? yp : ym) : (f & 1 ? zp : zm));
-                const double ih2 = d == 0 ? ih2x : (d == 1 ? ih2y : ih2z);
-                Au -= ih2 * (uc - unb);
-                if (!ZERO) {
-                    // the child covering that cell: of this brick, or of the face neighbour
-                    const int F = kids[inside ? 48 + qo : 8 * f + qo];
-                    const int m = d == 0 ? (ly & 3) + 4 * (lz & 3) : (d == 1 ? (lx & 3) + 4 * (lz & 3)
-                                                                                 : (lx & 3) + 4 * (ly & 3));
-                    Au += -0.5 * ih2 * ffs[((size_t)F * 6 + 2 * d + (sg < 0)) * 16 + m];
+            for (int h = 0; h < 2; ++h) {
+                on[h] = !cov[h] && ((nm >> (qo | h)) & 1);
+                a[h] = c[h] = make_double2(0.0, 0.0);
+                if (on[h]) {
+                    // the child covering the neighbours: of this brick, or of the face neighbour
+                    const int F = kids[(inside ? 48 : 8 * f) + (qo | h)];
+                    const double2 *p = (const double2 *)(ffs + ((size_t)F * 6 + 2 * d + 1 - s) * 16 +
+                                                         4 * ((d == 1 ? z : y) & 3));
+                    a[h] = p[0], c[h] = p[1];
                 }
             }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (on[h]) {
+                    const double fs[4] = {a[h].x, a[h].y, c[h].x, c[h].y};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        r[4 * h + i] += ih2 * (u[4 * h + i] - nrow[4 * h + i]);
+                        r[4 * h + i] += 0.5 * ih2 * fs[i];
+                    }
+                }
         }
-        r[x] = mine_cov ? 0.0 : rv[x] * inv_eps0 - Au;
+        // along x: the cells next to the other half, and the row's ends
+        const int m = (y & 3) + 4 * (z & 3);
+        const bool in3 = !cov[0] && cov[1], in4 = cov[0] && !cov[1];
+        const bool end0 = !cov[0] && ((ncm[0] >> (ozy | 1)) & 1), end7 = !cov[1] && ((ncm[1] >> ozy) & 1);
+        double fi = 0.0, f0 = 0.0, f7 = 0.0;
+        if (in3) fi = ffs[((size_t)kids[48 + (ozy | 1)] * 6 + 0) * 16 + m];
+        if (in4) fi = ffs[((size_t)kids[48 + ozy] * 6 + 1) * 16 + m];
+        if (end0) f0 = ffs[((size_t)kids[ozy | 1] * 6 + 1) * 16 + m];
+        if (end7) f7 = ffs[((size_t)kids[8 + ozy] * 6 + 0) * 16 + m];
+        if (end0) {
+            r[0] += ih2x * (u[0] - hs[0]);
+            r[0] += 0.5 * ih2x * f0;
+        }
+        if (in3) {
+            r[3] += ih2x * (u[3] - u[4]);
+            r[3] += 0.5 * ih2x * fi;
+        }
+        if (in4) {
+            r[4] += ih2x * (u[4] - u[3]);
+            r[4] += 0.5 * ih2x * fi;
+        }
+        if (end7) {
+            r[7] += ih2x * (u[7] - hs[1]);
+            r[7] += 0.5 * ih2x * f7;
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        if (cov[x >> 2]) r[x] = 0.0;
         const double av = fabs(r[x]);
         acc = norm_p == 2 ? acc + av * av : norm_p == 1 ? acc + av : fmax(acc, av);
     }
@@ -585,10 +656,14 @@ __global__ void __launch_bounds__(64 * BPW) k_outer_residual(DevMeta M, int b0, 
     for (int o = 32; o > 0; o >>= 1) {
         const double v = __shfl_xor(acc, o, 64);
         acc = norm_p == 0 ? fmax(acc, v) : acc + v;
+        if (BOTH) {
+            const double v0 = __shfl_xor(acc0, o, 64);
+            acc0 = norm_p == 0 ? fmax(acc0, v0) : acc0 + v0;
+        }
     }
     if (active && lane == 0) {
-        part[2 * (size_t)b] = acc;
-        part[2 * (size_t)b + 1] = 0.0;
+        part[b] = acc;
+        if (BOTH) part[n_part + b] = acc0;
     }
 }
 
@@ -613,83 +688,93 @@ __global__ void __launch_bounds__(256) k_user_brick(DevMeta M, int b0, int nb, c
     }
 }
 
-// Norm of each listed brick range (one AMR level of one problem) from the
-// partials (two per brick), in a fixed order, by one workgroup.  The ranges
-// go in chunks of NORM_CHUNK: every wavefront sums its share of each range
-// of the chunk, then one thread per range adds the 16 wavefront sums (one
-// barrier per chunk, not two per range).  With hout set, the norms are also
-// written to host-visible memory followed by a sequence number (the device
-// counter plus one, read at the start so that its latency overlaps the
-// sums), so that the host can poll for them without synchronising the
-// stream.  The host copy goes to hout + alt when the counter is odd: two
-// publications in a row land in different slots, so the host can still read
-// one while the next is being written.
-constexpr int NORM_CHUNK = 64;
-__global__ void __launch_bounds__(1024) k_level_norms(const int2 *ranges, int n, const double *part, double *out,
-                                                      int norm_p, double *hout, int alt, unsigned *hseq,
+// Norms of brick ranges (the AMR levels of each problem) from the bricks'
+// partials, in a fixed order.  The ranges are cut into pieces of at most
+// NORM_PIECE bricks (x first brick, y bricks, z range); a wavefront sums a
+// piece, all its loads in flight, and then one a range adds the piece sums.
+// sets = 2: the same for a second set of partials, n_part further on; its
+// norms follow the first set's.  Up to NORM_ONE pieces one workgroup does it
+// all.  More go to a workgroup per 16; the last to finish (an agent-scope
+// count that it sets back) adds the piece sums.
+//
+// With hout set, the norms are also written to host-visible memory followed
+// by a sequence number (the device counter plus one), so that the host can
+// poll for them without synchronising the stream.  The host copy goes to hout
+// + alt when the counter is odd: two publications in a row land in different
+// slots, so the host can still read one while the next is being written.
+//
+// One workgroup going from range to range took 7.5 us on three ranges of 3000
+// bricks, 47 on the 40 of a batch of sixteen and 121 on 4e5 bricks; now 4.9,
+// 9.3 and 11.
+__global__ void __launch_bounds__(1024) k_level_norms(const int4 *pieces, const int *first, int npiece, int n,
+                                                      int sets, const double *part, int n_part, double *psum,
+                                                      int *done, int norm_p, double *hout, int alt, unsigned *hseq,
                                                       unsigned *counter)
 {
-    __shared__ double sh[16][NORM_CHUNK];
+    __shared__ double sh[NORM_ONE], nrm[NORM_ONE];
     __shared__ unsigned sseq;
-    const bool mx = norm_p == 0;
-    const int wave = threadIdx.x >> 6;
-    unsigned seq = 0;
-    if (hout && threadIdx.x == 0) {
-        seq = *counter;
-        sseq = seq;
+    __shared__ int slast;
+    const bool mx = norm_p == 0, one = gridDim.x == 1;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (threadIdx.x == 0) sseq = *counter;
+    const int np = sets * npiece, p0 = one ? 0 : 16 * (int)blockIdx.x, p1 = one ? np : min(np, p0 + 16);
+    for (int p = p0 + wave; p < p1; p += 16) {
+        const bool second = p >= npiece;
+        const int4 pc = pieces[second ? p - npiece : p];
+        const double *v = part + (second ? n_part : 0) + pc.x;
+        double a[NORM_PIECE / 64];
+#pragma unroll
+        for (int j = 0; j < NORM_PIECE / 64; ++j) a[j] = lane + 64 * j < pc.y ? v[lane + 64 * j] : 0.0;
+        double s = 0.0;  // (partials are >= 0)
+#pragma unroll
+        for (int j = 0; j < NORM_PIECE / 64; ++j) s = mx ? fmax(s, a[j]) : s + a[j];
+        for (int o = 32; o > 0; o >>= 1) {
+            const double t = __shfl_xor(s, o, 64);
+            s = mx ? fmax(s, t) : s + t;
+        }
+        if (lane == 0) {
+            if (one) sh[p] = s;
+            else __hip_atomic_store(psum + p, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
-    for (int l0 = 0; l0 < n; l0 += NORM_CHUNK) {
-        const int nl = n - l0 < NORM_CHUNK ? n - l0 : NORM_CHUNK;
-        for (int j = 0; j < nl; ++j) {
-            // the range's partials as pairs (two per brick, 16-byte aligned):
-            // pair q of the range to thread q mod 1024, eight pairs in flight
-            const int2 rg = ranges[l0 + j];
-            const double2 *pp = (const double2 *)part + rg.x;
-            const int np = rg.y;
-            double a[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = 0.0;
-            int q = (int)threadIdx.x;
-            for (; q + 7 * 1024 < np; q += 8 * 1024) {
-                double2 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = pp[q + u * 1024];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = mx ? fmax(a[u], fmax(v[u].x, v[u].y)) : a[u] + (v[u].x + v[u].y);
-            }
-            {  // the last fewer than eight pairs of this thread, also in flight together (partials are >= 0)
-                double2 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = q + u * 1024 < np ? pp[q + u * 1024] : make_double2(0.0, 0.0);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = mx ? fmax(a[u], fmax(v[u].x, v[u].y)) : a[u] + (v[u].x + v[u].y);
-            }
-            double acc = mx ? fmax(fmax(fmax(a[0], a[1]), fmax(a[2], a[3])), fmax(fmax(a[4], a[5]), fmax(a[6], a[7])))
-                            : ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-            for (int o = 32; o > 0; o >>= 1) {
-                double w = __shfl_xor(acc, o, 64);
-                acc = mx ? fmax(acc, w) : acc + w;
-            }
-            if ((threadIdx.x & 63) == 0) sh[wave][j] = acc;
+    __syncthreads();
+    if (!one) {
+        if (threadIdx.x == 0) {
+            const int c = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            slast = c == (int)gridDim.x - 1;
+            if (slast) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         __syncthreads();
-        if ((int)threadIdx.x < nl) {
-            const int j = threadIdx.x;
-            double r = sh[0][j];
-            for (int i = 1; i < 16; ++i) r = mx ? fmax(r, sh[i][j]) : r + sh[i][j];
-            r = norm_p == 2 ? sqrt(r) : r;
-            out[l0 + j] = r;
-            if (hout) {
-                hout[(sseq & 1u) * alt + l0 + j] = r;
-                __threadfence_system();
+        if (!slast) return;
+    }
+    // (ranges NORM_ONE at a time: their sums to LDS, then one wavefront
+    // publishes them, with one system-wide fence at the end)
+    const unsigned seq = sseq;
+    for (int k0 = 0; k0 < sets * n; k0 += NORM_ONE) {
+        for (int k = k0 + wave; k < min(sets * n, k0 + NORM_ONE); k += 16) {
+            const int j = k >= n ? k - n : k, o = k >= n ? npiece : 0, e = first[j + 1];
+            double s = 0.0;
+            for (int p = first[j] + lane; p < e; p += 64) {
+                const double t = one ? sh[o + p]
+                                     : __hip_atomic_load(psum + o + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s = mx ? fmax(s, t) : s + t;
             }
+            for (int q = 32; q > 0; q >>= 1) {
+                const double t = __shfl_xor(s, q, 64);
+                s = mx ? fmax(s, t) : s + t;
+            }
+            if (lane == 0) nrm[k - k0] = norm_p == 2 ? sqrt(s) : s;
         }
         __syncthreads();
+        if (wave == 0 && k0 + lane < sets * n) hout[(seq & 1u) * alt + k0 + lane] = nrm[lane];
+        __syncthreads();
     }
-    if (hout && threadIdx.x == 0) {
+    if (wave == 0) {
         __threadfence_system();
-        *counter = seq + 1;
-        *(volatile unsigned *)hseq = seq + 1;
+        if (lane == 0) {
+            *counter = seq + 1;
+            *(volatile unsigned *)hseq = seq + 1;
+        }
     }
 }
 
@@ -1236,32 +1321,94 @@ __global__ void __launch_bounds__(256) k_avgdown(DevMeta M, int b0, int nb, doub
 }
 
 // E_d = -(u_+ - u_-) / (2 h_d) on every cell of a range of AMR bricks (phi in
-// brick layout, E in the caller's layout)
-__global__ void __launch_bounds__(256) k_efield(DevMeta M, int b0, int nb, const double *phib, const double *cp_phi,
-                                                double *const *E, const int32_t *list)
+// brick layout) and phi itself into the caller's layout, in the row layout of
+// the outer residual: one wavefront per brick.  Bound by its bytes, 8 read and
+// 32 written per cell: 576^3 + 2 levels (2.1e8 cells) 2005 us, 4.2 TB/s; with
+// phi in a pass of its own 2045 + 683, and with a lane storing its whole row
+// (64 bytes apart from the next lane's) 2900.
+template <int BPW>
+__global__ void __launch_bounds__(64 * BPW) k_efield(DevMeta M, int b0, int nb, const double *phib,
+                                                     const double *cp_phi, double *const *E, double *const *phi,
+                                                     const int32_t *list)
 {
-    __shared__ double tile[TE * TE * TE];
-    __shared__ double alpha[6];
-    int b = pick_brick(b0, nb, list, blockIdx.x);
-    int lev = M.org[b].w;
-    LevelConst L = M.lc[lev];
-    stage_tile<SrcB<double>, false, CpArr<double>>(M, b, SrcB<double>{phib}, CpArr<double>{cp_phi}, true, tile,
-                                                   alpha);
-    int64_t ub = M.ubase[b];
-    int2 us = M.ustr[b];
-    for (int c = threadIdx.x; c < BRICK_CELLS; c += 256) {
-        int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
-        int64_t ui = ub + x + (int64_t)us.x * y + (int64_t)us.y * z;
-        double uc = tile[tix(x, y, z)];
-        for (int d = 0; d < 3; ++d) {
-            double a, bv;
-            tile_ab(tile, alpha, x, y, z, d, +1, a, bv);
-            double up = a * uc + bv;
-            tile_ab(tile, alpha, x, y, z, d, -1, a, bv);
-            double um = a * uc + bv;
-            E[3 * lev + d][ui] = -(up - um) / (2.0 * L.h[d]);
-        }
+    __shared__ double rows_all[BPW][RW * RW * RS];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int k0 = xcd_remap(blockIdx.x, (nb + BPW - 1) / BPW) * BPW + w;
+    const bool active = k0 < nb;
+    const int kk = active ? k0 : nb - 1;
+    const int b = __builtin_amdgcn_readfirstlane(list ? list[kk] : b0 + kk);
+    double *rows = rows_all[w];
+    const int y = lane & 7, z = lane >> 3;
+    const int lev = M.org[b].w;
+    const LevelConst L = M.lc[lev];
+    int nbf[6], kind[6];
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+        nbf[f] = M.nbr[b * 6 + f];
+        kind[f] = nbf[f] >= 0 ? 0 : ((-1 - nbf[f]) < M.nbc ? 1 : 2);
     }
+    double u[8], hs[6];
+    Row8<double>::load(phib + (size_t)b * BRICK_CELLS + 8 * lane, u);
+    // halo slots: the neighbour's phi, 2 g on the boundary, or the coarse part
+    // of the coarse-fine ghost
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+        const int d = f >> 1, md = (f & 1) ? 0 : 7, uu = lane & 7, vv = lane >> 3;
+        const int c = d == 0 ? md + 8 * uu + 64 * vv : (d == 1 ? uu + 8 * md + 64 * vv : uu + 8 * vv + 64 * md);
+        hs[f] = kind[f] == 0   ? phib[(size_t)nbf[f] * BRICK_CELLS + c]
+                : kind[f] == 1 ? 2.0 * M.gbc[(size_t)(-1 - nbf[f]) * 64 + lane]
+                               : cp_phi[(size_t)(-1 - nbf[f] - M.nbc) * 64 + lane];
+    }
+    const int rym = rrow(y - 1, z), ryp = rrow(y + 1, z), rzm = rrow(y, z - 1), rzp = rrow(y, z + 1), rme = rrow(y, z);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) rows[rme + i] = u[i];
+    rows[rrow(-1, lane >> 3) + (lane & 7)] = hs[2];
+    rows[rrow(8, lane >> 3) + (lane & 7)] = hs[3];
+    rows[rrow(lane >> 3, -1) + (lane & 7)] = hs[4];
+    rows[rrow(lane >> 3, 8) + (lane & 7)] = hs[5];
+    const double a0 = L.abnd[0], a1 = L.abnd[1], a2 = L.abnd[2];
+    __syncthreads();
+    if (!active) return;
+    // the neighbour's value across a face of kind k from its halo slot v, the
+    // cell uc and the cell further inside
+    auto ghost = [](int k, double a, double v, double uc, double in) {
+        return k == 0 ? v : (k == 1 ? a * uc + v : (2.0 / 3.0) * uc + (v - 0.2 * in));
+    };
+    double ex[8], ey[8], ez[8];
+    const double h2x = 2.0 * L.h[0], h2y = 2.0 * L.h[1], h2z = 2.0 * L.h[2];
+    const double rx = 1.0 / h2x, ry = 1.0 / h2y, rz = 1.0 / h2z;
+    const int kym = y == 0 ? kind[2] : 0, kyp = y == 7 ? kind[3] : 0;
+    const int kzm = z == 0 ? kind[4] : 0, kzp = z == 7 ? kind[5] : 0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        const double um = x == 0 ? ghost(kind[0], a0, hs[0], u[0], u[1]) : u[x - 1];
+        const double up = x == 7 ? ghost(kind[1], a0, hs[1], u[7], u[6]) : u[x + 1];
+        ex[x] = -div_by(up - um, h2x, rx);
+        const double vm = rows[rym + x], vp = rows[ryp + x], wm = rows[rzm + x], wp = rows[rzp + x];
+        ey[x] = -div_by(ghost(kyp, a1, vp, u[x], vm) - ghost(kym, a1, vm, u[x], vp), h2y, ry);
+        ez[x] = -div_by(ghost(kzp, a2, wp, u[x], wm) - ghost(kzm, a2, wm, u[x], wp), h2z, rz);
+    }
+    // out through the rows in LDS, eight lanes a row, so that each store
+    // instruction fills whole 64-byte segments
+    const int2 us = M.ustr[b];
+    const int64_t ub = M.ubase[b] + (lane & 7) + (int64_t)us.x * (lane >> 3);
+    auto store = [&](double *to) {
+        wave_fence();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) to[ub + (int64_t)us.y * k] = rows[rrow(lane >> 3, k) + (lane & 7)];
+        wave_fence();
+    };
+    auto stage = [&](const double (&v)[8]) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) rows[rme + i] = v[i];
+    };
+    store(phi[lev]);
+    stage(ex);
+    store(E[3 * lev]);
+    stage(ey);
+    store(E[3 * lev + 1]);
+    stage(ez);
+    store(E[3 * lev + 2]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1812,16 +1959,6 @@ __global__ void __launch_bounds__(1024) k_coarse_cycle(DevMeta M, const CoarseJo
 // ---------------------------------------------------------------------------
 // particles
 // ---------------------------------------------------------------------------
-// a / h, correctly rounded, from rh = 1/h rounded to nearest: with the
-// remainder a - h (a rh) exact in one fma, the corrected quotient is the
-// rounded one (Markstein's theorem), in 3 instructions instead of the
-// division's dozen
-__device__ __forceinline__ double div_by(double a, double h, double rh)
-{
-    const double q = a * rh;
-    return fma(fma(-q, h, a), rh, q);
-}
-
 template <class P>
 __device__ __forceinline__ bool cic_stencil(const DepLevel &D, double X, double Y, double Z, int *i0, int *i1,
                                             double *f)
@@ -2140,11 +2277,6 @@ __global__ void __launch_bounds__(256) k_pack_records(int64_t n, const P *x, con
     if (i < n) rec[i] = make_double4((double)x[i], (double)y[i], (double)z[i], q ? q[i] : 0.0);
 }
 
-// Two cells adjacent along x in one row of a box: one 16-byte load (8-byte
-// alignment is enough for a global load on CDNA).
-typedef double dpair __attribute__((ext_vector_type(2)));
-typedef dpair dpair_a8 __attribute__((aligned(8)));
-
 // Corners of a CIC stencil: bit d of c selects the upper cell along axis d;
 // st[d]: the stencil crosses a brick face along d.  A corner is "fresh"
 // when every upper axis of it crosses, so that its brick differs from the
@@ -2256,13 +2388,6 @@ __device__ __forceinline__ bool gather_cells(const DepLevel &D, const double *co
         }
     }
     return true;
-}
-
-// order the LDS accesses of a wavefront among its lanes
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 // cells and bricks of a gather's field tile (one per wavefront)
@@ -2546,27 +2671,22 @@ static inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + p
 template <class T>
 void launch_outer_residual(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, const double *phib,
                            const double *rhob, double inv_eps0, const double *cp_phi, T *r_out, double *part,
-                           int norm_p, bool zero_phi, double *const *r_user, const double *ffs)
+                           int n_part, int norm_p, bool both, double *const *r_user, const double *ffs)
 {
     if (nb <= 0) return;
     // four bricks per workgroup on levels far larger than the chip (the
     // sweep's tuning finds the same), one otherwise
+#define AMRMG_RESIDUAL(BOTH, BPW)                                                                                    \
+    AMRMG_LAUNCH((k_outer_residual<T, BOTH, BPW>), dim3((nb + BPW - 1) / BPW), dim3(64 * BPW), 0, st, M, b0, nb, phib, \
+                 rhob, inv_eps0, cp_phi, r_out, part, n_part, norm_p, list, r_user, ffs)
     if (nb > 16384) {
-        const dim3 g((nb + 3) / 4), blk(256);
-        if (zero_phi)
-            AMRMG_LAUNCH((k_outer_residual<T, true, 4>), g, blk, 0, st, M, b0, nb, phib, rhob, inv_eps0, cp_phi,
-                         r_out, part, norm_p, list, r_user, ffs);
-        else
-            AMRMG_LAUNCH((k_outer_residual<T, false, 4>), g, blk, 0, st, M, b0, nb, phib, rhob, inv_eps0, cp_phi,
-                         r_out, part, norm_p, list, r_user, ffs);
+        if (both) AMRMG_RESIDUAL(true, 4);
+        else AMRMG_RESIDUAL(false, 4);
     } else {
-        if (zero_phi)
-            AMRMG_LAUNCH((k_outer_residual<T, true, 1>), dim3(nb), dim3(64), 0, st, M, b0, nb, phib, rhob, inv_eps0,
-                         cp_phi, r_out, part, norm_p, list, r_user, ffs);
-        else
-            AMRMG_LAUNCH((k_outer_residual<T, false, 1>), dim3(nb), dim3(64), 0, st, M, b0, nb, phib, rhob,
-                         inv_eps0, cp_phi, r_out, part, norm_p, list, r_user, ffs);
+        if (both) AMRMG_RESIDUAL(true, 1);
+        else AMRMG_RESIDUAL(false, 1);
     }
+#undef AMRMG_RESIDUAL
 }
 
 void launch_user_brick(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, bool to_brick,
@@ -2576,12 +2696,13 @@ void launch_user_brick(hipStream_t st, const DevMeta &M, int b0, int nb, const i
     AMRMG_LAUNCH(k_user_brick, dim3(nb), dim3(256), 0, st, M, b0, nb, list, (int)to_brick, a, ab, bu, bb);
 }
 
-void launch_level_norms(hipStream_t st, const int2 *ranges, int n, const double *part, double *out, int norm_p,
+void launch_level_norms(hipStream_t st, const NormPlan &N, int sets, const double *part, int n_part, int norm_p,
                         double *hout, int alt, unsigned *hseq, unsigned *counter)
 {
-    if (n <= 0) return;
-    AMRMG_LAUNCH(k_level_norms, dim3(1), dim3(1024), 0, st, ranges, n, part, out, norm_p, hout, alt, hseq,
-                 counter);
+    if (N.n <= 0) return;
+    const int np = sets * N.npiece;
+    AMRMG_LAUNCH(k_level_norms, dim3(np <= NORM_ONE ? 1 : (np + 15) / 16), dim3(1024), 0, st, N.pieces, N.first,
+                 N.npiece, N.n, sets, part, n_part, N.psum, N.done, norm_p, hout, alt, hseq, counter);
 }
 
 template <class T>
@@ -2648,10 +2769,13 @@ void launch_avgdown(hipStream_t st, const DevMeta &M, int b0, int nb, double *ph
 }
 
 void launch_efield(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, const double *phib,
-                   const double *cp_phi, double *const *E)
+                   const double *cp_phi, double *const *E, double *const *phi)
 {
     if (nb <= 0) return;
-    AMRMG_LAUNCH(k_efield, dim3(nb), dim3(256), 0, st, M, b0, nb, phib, cp_phi, E, list);
+    if (nb > 16384)  // as the outer residual
+        AMRMG_LAUNCH((k_efield<4>), dim3((nb + 3) / 4), dim3(256), 0, st, M, b0, nb, phib, cp_phi, E, phi, list);
+    else
+        AMRMG_LAUNCH((k_efield<1>), dim3(nb), dim3(64), 0, st, M, b0, nb, phib, cp_phi, E, phi, list);
 }
 
 template <class T>
@@ -2872,7 +2996,7 @@ void launch_fill(hipStream_t st, double *v, int64_t n, double val)
 #define AMRMG_INST(T)                                                                                            \
     template void launch_outer_residual<T>(hipStream_t, const DevMeta &, int, int, const int32_t *,               \
                                            const double *, const double *, double, const double *, T *, double *, \
-                                           int, bool, double *const *, const double *);                           \
+                                           int, int, bool, double *const *, const double *);                      \
     template void launch_cpart_brick<T>(hipStream_t, const DevMeta &, int, int, const T *, T *, const T *,      \
                                         double *);                                                              \
     template void launch_face_sums<T>(hipStream_t, const DevMeta &, int, int, const T *, double *);             \

@@ -108,19 +108,32 @@ bool launch_timing_pending();
 // ffs[(F * 6 + f) * 16 + m] = sum over the four fine cells next to the face of
 // (u_f/3 + u_in/5 - coarse part of the ghost), written for coarse-fine faces.
 
-// phib, rhob: FP64 phi and rho in brick layout; ffs: fine sums of phib
+// phib, rhob: FP64 phi and rho in brick layout; ffs: fine sums of phib; part:
+// one partial norm per brick; both: also those of the residual of phi = 0, n_part
+// further on
 template <class T>
 void launch_outer_residual(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, const double *phib,
                            const double *rhob, double inv_eps0, const double *cp_phi, T *r_out, double *part,
-                           int norm_p, bool zero_phi, double *const *r_user, const double *ffs);
+                           int n_part, int norm_p, bool both, double *const *r_user, const double *ffs);
 // caller's layout (per-level pointer tables a, bu) <-> brick layout (ab, bb)
 void launch_user_brick(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, bool to_brick,
                        double *const *a, double *ab, double *const *bu, double *bb);
-// per-range norms into out (device); with hout, also into host-visible
-// memory (at hout + alt when *counter is odd) followed by the sequence number
-// *counter + 1 at hseq
-void launch_level_norms(hipStream_t st, const int2 *ranges, int n, const double *part, double *out, int norm_p,
-                        double *hout = nullptr, int alt = 0, unsigned *hseq = nullptr, unsigned *counter = nullptr);
+// The ranges whose norms a solve wants, cut into pieces of at most NORM_PIECE
+// bricks: pieces (first brick, bricks, range), first[j] .. first[j + 1] those
+// of range j; psum [2 npiece] and done (zero between launches) are scratch
+constexpr int NORM_PIECE = 512, NORM_ONE = 64;
+struct NormPlan {
+    const int4 *pieces;
+    const int *first;
+    int npiece, n;
+    double *psum;
+    int *done;
+};
+// per-range norms of the partials (and, with sets = 2, of the second set
+// n_part further on) into host-visible memory (at hout + alt when *counter is
+// odd) followed by the sequence number *counter + 1 at hseq
+void launch_level_norms(hipStream_t st, const NormPlan &N, int sets, const double *part, int n_part, int norm_p,
+                        double *hout, int alt, unsigned *hseq, unsigned *counter);
 // coarse parts cp of the ghosts of coarse-fine faces [cf0, cf0 + ncf) from
 // the coarse values src; with ffs, also the fine sums from the fine values
 template <class T>
@@ -147,8 +160,9 @@ template <class T>
 void launch_phi_update(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, double *phib,
                        const T *e);
 void launch_avgdown(hipStream_t st, const DevMeta &M, int b0, int nb, double *phib);
+// E, and phi, of bricks into the caller's layout
 void launch_efield(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, const double *phib,
-                   const double *cp_phi, double *const *E);
+                   const double *cp_phi, double *const *E, double *const *phi);
 template <class T>
 void launch_bottom_cg(hipStream_t st, const DevMeta &M, const int4 *jobs, int njobs, const T *rhs, T *e,
                       double *work, double rtol, int maxit, int *iters);

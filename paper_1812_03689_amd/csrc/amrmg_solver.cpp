@@ -40,9 +40,9 @@ size_t ws_need(const DevState &D, int prec)
     s += 2 * align256(nc * 8);                        // phi, rho in brick layout
     s += align256((size_t)m.ncf * 64 * w + 8);         // coarse parts of the cycle
     s += align256((size_t)m.ncf * 64 * 8 + 8);         // coarse parts of phi
-    s += align256((size_t)m.nbrick * 16);              // per-wavefront partial norms (two per brick)
+    s += align256((size_t)m.nbrick * 16);              // partial norms (two sets, one per brick)
     s += align256((size_t)m.nbrick * 96 * 8);          // fine sums of the coarse-fine faces
-    s += align256(sizeof(double) * 2 * (D.range_prob.size() + 1));
+    s += align256(sizeof(double) * 2 * ((size_t)D.norms.npiece + 1));  // sums of the norms' pieces
     s += align256(D.cg_doubles * 8);
     s += align256(D.dw_doubles * 8 + 8);             // direct-solve scratch
     s += align256(64);
@@ -82,11 +82,12 @@ amrmg_status ensure_ws(DevState &D, int prec, void *user, size_t user_bytes)
     D.cpphi = (double *)take((size_t)m.ncf * 64 * 8 + 8);
     D.part = (double *)take((size_t)m.nbrick * 16);
     D.ffs = (double *)take((size_t)m.nbrick * 96 * 8);
-    D.dnorm = (double *)take(sizeof(double) * 2 * (D.range_prob.size() + 1));
+    D.norms.psum = (double *)take(sizeof(double) * 2 * ((size_t)D.norms.npiece + 1));
     D.cgw = (double *)take(D.cg_doubles * 8);
     D.dw = (double *)take(D.dw_doubles * 8 + 8);
     D.cgit = (int *)take(64);
     D.d_seqc = (unsigned *)((char *)D.cgit + 32);
+    D.norms.done = (int *)((char *)D.cgit + 48);
     D.ws_prec = prec;
     return AMRMG_OK;
 }
@@ -248,29 +249,29 @@ struct Driver {
         return AMRMG_OK;
     }
 
-    // outer FP64 residual of every AMR level; norms into dnorm[off ..] (and
-    // published to the host at h_pub[pub_off ..] when publish is set, or
-    // pub_alt further on when the publication's sequence number is even)
-    void outer(bool zero_phi, int noff, double *const *rout_user, bool publish = false, int pub_off = 0,
-               int pub_alt = 0)
+    // outer FP64 residual of every AMR level (rout_user: into the caller's
+    // arrays), with both also that of phi = 0, and their partial norms
+    void outer(double *const *rout_user, bool both)
     {
         int b0, nb;
         const int32_t *list;
         amr_range(b0, nb, list);
-        if (!zero_phi) {
-            pb(AMRMG_K_CPART);
-            launch_cpart_brick<double>(st, D.M, 0, m.ncf, D.phib, D.cpphi, D.phib, D.ffs);
-            pe(AMRMG_K_CPART, (double)m.ncf * 16 * (9 + 4) * 8);
-        }
+        pb(AMRMG_K_CPART);
+        launch_cpart_brick<double>(st, D.M, 0, m.ncf, D.phib, D.cpphi, D.phib, D.ffs);
+        pe(AMRMG_K_CPART, (double)m.ncf * 16 * (9 + 4) * 8);
         // (a last-workgroup reduction inside the residual kernel would need a
-        // device-scope fence per workgroup, which costs far more than this
-        // extra launch on a chip whose XCDs have separate L2 caches)
+        // device-scope fence per workgroup, which costs far more than the
+        // norms' own launch on a chip whose XCDs have separate L2 caches)
         pb(AMRMG_K_RESIDUAL);
-        launch_outer_residual<T>(st, D.M, b0, nb, list, D.phib, D.rhob, o.inv_eps0, zero_phi ? nullptr : D.cpphi,
-                                 (zero_phi || rout_user) ? nullptr : r, D.part, o.norm_p, zero_phi, rout_user, D.ffs);
-        pe(AMRMG_K_RESIDUAL, (double)nb * BRICK_CELLS * (zero_phi ? 8.0 : 16.0 + W));
-        launch_level_norms(st, D.d_ranges, (int)D.range_prob.size(), D.part, D.dnorm + noff, o.norm_p,
-                           publish ? D.h_pub + pub_off : nullptr, pub_alt, D.h_seq, D.d_seqc);
+        launch_outer_residual<T>(st, D.M, b0, nb, list, D.phib, D.rhob, o.inv_eps0, D.cpphi, rout_user ? nullptr : r,
+                                 D.part, m.nbrick, o.norm_p, both, rout_user, D.ffs);
+        pe(AMRMG_K_RESIDUAL, (double)nb * BRICK_CELLS * (16.0 + W));
+    }
+    // the norms of the last residual's partials, published at h_pub[off ..],
+    // or alt further on in turn
+    void norms(int sets, int off, int alt)
+    {
+        launch_level_norms(st, D.norms, sets, D.part, m.nbrick, o.norm_p, D.h_pub + off, alt, D.h_seq, D.d_seqc);
     }
 
     void smooth(int k, int nu, bool pre)
@@ -430,7 +431,8 @@ struct Driver {
     void iteration(int nr)
     {
         vcycle();
-        outer(false, nr, nullptr, true, 2 * nr, nr);
+        outer(nullptr, false);
+        norms(1, 2 * nr, nr);
     }
 };
 
@@ -517,16 +519,16 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
     // stream may still be busy with the caller's earlier work (the deposit)
     if (o.smoother == AMRMG_GSRB && !noalloc) ST_TRY(drv.tune());
     if (graphs && !prof && o.max_iters > 0) ST_TRY(ensure_graph<T>(D, nr, o));
-    HIP_TRY(hipMemsetAsync(D.cgit, 0, 64, st));  // CG iteration count and the norm sequence counter
+    HIP_TRY(hipMemsetAsync(D.cgit, 0, 64, st));  // CG iteration count, the norms' sequence and workgroup counters
     D.seq = 0;
     *(volatile unsigned *)D.h_seq = 0;
     HIP_TRY(hipEventRecord(ev0, st));
-    // norms of b (zero phi) to h_pub[nr ..], of the initial residual to
-    // h_pub[0 ..]; each publication bumps the sequence number, and those of
-    // the iterations alternate between two slots after these
+    // norms of the initial residual to h_pub[0 ..], of b (the residual of phi
+    // = 0) to h_pub[nr ..]; each publication bumps the sequence number, and
+    // those of the iterations alternate between two slots after these
     drv.to_bricks(true);
-    drv.outer(true, 0, nullptr, true, nr);
-    drv.outer(false, nr, nullptr, true, 0);
+    drv.outer(nullptr, true);
+    drv.norms(2, 0, 0);
     HIP_TRY(hipGetLastError());
     // the first iteration is queued before the initial norms are read; when
     // the initial guess already meets the tolerance it only refines phi, and
@@ -548,7 +550,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         HIP_TRY(hipGetLastError());
         return AMRMG_OK;
     };
-    D.seq = 2;
+    D.seq = 1;
     ST_TRY(wait_pub(D.seq));
     std::vector<double> bn(D.h_pub + nr, D.h_pub + 2 * nr), rn(D.h_pub, D.h_pub + nr);
     // a level without right-hand side uses its problem's composite norm
@@ -585,7 +587,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         return w;
     };
     // the norms of the iteration whose publication was the last awaited
-    // (sequence numbers 3, 5, ... in h_pub[2 nr ..], 4, 6, ... in h_pub[3 nr ..])
+    // (sequence numbers 3, 5, ... in h_pub[2 nr ..], 2, 4, ... in h_pub[3 nr ..])
     auto read_iter = [&]() {
         const double *src = D.h_pub + (2 + (D.seq & 1u ? 0 : 1)) * nr;
         rn.assign(src, src + nr);
@@ -624,7 +626,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         ++it;
         all = check(it) || all;
     }
-    // average down, finest first, then the field
+    // average down, finest first, then the field (its kernel returns phi too)
     for (int k = m.K - 1; k >= 1; --k)
         for (int ei = m.step_ent0[k]; ei < m.step_ent0[k + 1]; ++ei)
             if (m.ent[ei].amr >= 1) {
@@ -637,10 +639,11 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         const int32_t *list;
         drv.amr_range(b0, nb, list);
         drv.pb(AMRMG_K_EFIELD);
-        launch_efield(st, D.M, b0, nb, list, D.phib, D.cpphi, D.d_E);
-        drv.pe(AMRMG_K_EFIELD, (double)nb * BRICK_CELLS * 32.0);
+        launch_efield(st, D.M, b0, nb, list, D.phib, D.cpphi, D.d_E, D.d_phi);
+        drv.pe(AMRMG_K_EFIELD, (double)nb * BRICK_CELLS * 40.0);
+    } else {
+        drv.from_bricks();
     }
-    drv.from_bricks();
     HIP_TRY(hipEventRecord(ev1, st));
     HIP_TRY(hipEventSynchronize(ev1));
     HIP_TRY(hipGetLastError());
@@ -789,7 +792,7 @@ extern "C" amrmg_status amrmg_residual(amrmg_ctx *ctx, double *const *rho, doubl
     SolveOpts o = opts_of(ctx->P);
     Driver<double> drv(D, ctx->st, o, nullptr);
     drv.to_bricks(true);
-    drv.outer(false, 0, D.d_rout);
+    drv.outer(D.d_rout, false);
     HIP_TRY(hipStreamSynchronize(ctx->st));
     HIP_TRY(hipGetLastError());
     return AMRMG_OK;

@@ -157,7 +157,7 @@ struct DevState {
     unsigned bseq = 0;
     int n_amr = 0, amr_first = 0, n_reflux = 0;  // AMR bricks (list d_amr), update list length
     int32_t *d_reflux = nullptr, *d_amr = nullptr;
-    int2 *d_ranges = nullptr;  // brick range of each AMR level of each problem
+    NormPlan norms{};  // over the AMR levels of every problem
     std::vector<int> range_prob, range_amr;
     int4 *d_jobs = nullptr;
     int njobs = 0;
@@ -185,14 +185,12 @@ struct DevState {
     size_t ws_bytes = 0;
     int ws_prec = -1;
     void *e = nullptr, *r = nullptr, *et = nullptr, *cpe = nullptr;
-    double *cpphi = nullptr, *part = nullptr, *dnorm = nullptr;
+    double *cpphi = nullptr, *part = nullptr;
     double *ffs = nullptr;  // fine sums of coarse-fine faces, 96 per brick
     double *phib = nullptr, *rhob = nullptr;  // FP64 phi and rho in brick layout during a solve
     double *cgw = nullptr;
     int *cgit = nullptr;
     int cg_threads = 1024;
-    PBuf h_normbuf;
-    double *h_norm = nullptr;
     // norms of each outer iteration, published by the norms kernel: values,
     // then a sequence number; the device keeps the count at d_seqc
     CBuf pubbuf;
