@@ -650,7 +650,7 @@ def main():
     prof_all = {c: amrmg.amrmg_profile_read(cm.h, c) for c in amrmg.KCLASS}
     dominant = max(prof_all, key=lambda c: prof_all[c]["ms"])
 
-    # timed region (no profiling: the outer iterations replay as a graph)
+    # timed region (no profiling)
     amrmg.amrmg_profile_enable(cm.h, [])
     step()
     torch.cuda.synchronize()

@@ -254,12 +254,12 @@ amrmg_status amrmg_solve(amrmg_ctx *ctx, double *const *rho, double *const *phi,
 /* For callers that cannot allocate device memory (code that runs under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
  * solve of amrmg_solve, same arguments, same results, that allocates no
- * device or pinned host memory and instantiates no graph.  Its workspace is
+ * device or pinned host memory.  Its workspace is
  * carved from a file-scope device array of AMRMG_NOALLOC_SCRATCH_BYTES
  * (128 MiB) that the library's code object holds on every GPU it runs on
  * until the process ends; the array's address on a device is looked up once,
  * when the first context on that device is created.  The cycle is launched
- * kernel by kernel (no graph replay), with the sweep shapes amrmg_solve has
+ * as amrmg_solve's, with the sweep shapes amrmg_solve has
  * tuned so far or the size rule.  The hierarchy must have been built
  * (amrmg_build_hierarchy allocates); a hierarchy whose workspace
  * (amrmg_workspace_size) exceeds the array gives AMRMG_E_OOM with phi, E

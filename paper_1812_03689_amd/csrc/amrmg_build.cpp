@@ -215,11 +215,12 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         D.cg_threads = maxn <= 512 ? 512 : 1024;
     }
     static thread_local std::vector<CoarseJob> cj;
-    static thread_local std::vector<double> dtab;
+    static thread_local std::vector<double> tkey;  // edges, spacings and ghosts of the direct grids
+    size_t ntab = 0;
     static thread_local std::vector<DirectJob> djl;
     static thread_local std::vector<int2> planes, groups;
     cj.assign(m.prob_ent.size(), CoarseJob{});
-    dtab.clear();
+    tkey.clear();
     djl.clear();
     planes.clear();
     groups.clear();
@@ -251,13 +252,16 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
             J.dn[d] = L.n[d];
             D.direct_maxdim = std::max(D.direct_maxdim, L.n[d]);
         }
-        J.tab = (int)dtab.size();
+        J.tab = (int)ntab;
         J.w = (int)D.dw_doubles;
         J.amr = L.amr >= 0 ? 1 : 0;
         double ab[3];
         boundary_ghost(*probs[e0.prob], L.h, ab);
-        const std::vector<double> &t = cached_direct_tables(L.n, L.h, ab);
-        append_padded_tables(dtab, L.n, t);
+        for (int d = 0; d < 3; ++d) {
+            tkey.insert(tkey.end(), {(double)L.n[d], L.h[d], ab[d]});
+            const size_t pad = ((size_t)L.n[d] + 15) & ~(size_t)15;
+            ntab += 2 * pad * pad + (size_t)L.n[d];
+        }
         D.dw_doubles += (size_t)L.n[0] * L.n[1] * L.n[2];
         const int jid = (int)djl.size();
         djl.push_back(J);
@@ -270,7 +274,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.n_groups = (int)groups.size();
     D.n_djobs = (int)djl.size();
     if (D.n_djobs == 1) D.djob0 = djl[0];
-    if (dtab.empty()) dtab.push_back(0.0);
     if (djl.empty()) djl.push_back(DirectJob{});
     if (planes.empty()) planes.push_back(make_int2(0, 0));
     if (groups.empty()) groups.push_back(make_int2(0, 0));
@@ -289,7 +292,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     EntryDev *dent = nullptr;
     BoxDev *dbox = nullptr;
     double *dmono = nullptr;
-    P.add(dtab, &D.d_dtab);
     P.add(djl, &D.d_djobs);
     P.add(planes, &D.d_planes);
     P.add(groups, &D.d_groups);
@@ -297,6 +299,22 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     P.add(bx, &dbox);
     P.add(mono, &dmono);
     ST_TRY(P.run(D.metabuf, D.stage, st));
+    if (D.dtab_key != tkey || !D.dtabbuf.p) {
+        std::vector<double> dtab;
+        dtab.reserve(ntab + 1);
+        for (size_t k = 0; k < tkey.size(); k += 9) {
+            const int n[3] = {(int)tkey[k], (int)tkey[k + 3], (int)tkey[k + 6]};
+            const double h[3] = {tkey[k + 1], tkey[k + 4], tkey[k + 7]}, ab[3] = {tkey[k + 2], tkey[k + 5], tkey[k + 8]};
+            append_padded_tables(dtab, n, cached_direct_tables(n, h, ab));
+        }
+        if (dtab.empty()) dtab.push_back(0.0);
+        D.dtab_key.clear();
+        HIP_TRY(D.dtabbuf.ensure(sizeof(double) * dtab.size()));
+        HIP_TRY(hipMemcpyAsync(D.dtabbuf.p, dtab.data(), sizeof(double) * dtab.size(), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));  // (the source ends here)
+        D.dtab_key = tkey;
+    }
+    D.d_dtab = (double *)D.dtabbuf.p;
 
     // brick tables on the device
     const int nbr_ = m.nbrick, nent = (int)m.ent.size();
@@ -433,8 +451,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.h_seq = (unsigned *)D.pubbuf.p;
     D.h_pub = (double *)D.pubbuf.p + 1;
     D.ws_prec = -1;  // carve the workspace again for the new hierarchy
-    D.drop_graph();
-    ++D.meta_gen;
     return AMRMG_OK;
 }
 

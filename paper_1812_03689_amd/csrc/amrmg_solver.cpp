@@ -119,8 +119,6 @@ extern "C" amrmg_status amrmg_set_workspace(amrmg_ctx *ctx, void *dev, size_t by
 // ---------------------------------------------------------------------------
 // the solve
 // ---------------------------------------------------------------------------
-// replay the outer iteration as a hipGraph (AMRMG_NO_GRAPH=1 disables)
-static bool g_use_graphs = getenv("AMRMG_NO_GRAPH") == nullptr;
 // an outer iteration is queued one ahead while the residual is this many
 // times above its target (a cycle reduces it by far less than this factor)
 constexpr double kAhead = 100.0;
@@ -129,9 +127,8 @@ constexpr double kAhead = 100.0;
 // bricks per workgroup), tuned on the device: for each launch size class
 // (bricks per launch, rounded up to a power of two) and cycle precision the
 // first solve that meets it times a plain sweep with each shape and keeps the
-// fastest unless the size rule's is within 3 %; later solves and captured
-// graphs read the choice.  Process-wide (one GPU per process);
-// AMRMG_NO_TUNE=1 keeps the size rule instead.
+// fastest unless the size rule's is within 3 %; later solves read the choice.
+// Process-wide (one GPU per process); AMRMG_NO_TUNE=1 keeps the size rule instead.
 static std::mutex g_tune_mu;
 static std::map<std::pair<int, int>, int> g_hgs_nt;  // (sizeof(T), log2 bricks) -> threads per workgroup
 static const bool g_tune = getenv("AMRMG_NO_TUNE") == nullptr;
@@ -436,46 +433,6 @@ struct Driver {
     }
 };
 
-// The graph of one outer iteration, captured and instantiated once per
-// hierarchy, workspace and option set; iterate launches it (or the kernels
-// themselves when graphs are off or launches are being timed).
-template <class T>
-static amrmg_status ensure_graph(DevState &D, int nr, const SolveOpts &o)
-{
-    std::vector<int64_t> key = {D.meta_gen, (int64_t)(intptr_t)D.ws, (int64_t)sizeof(T), o.smoother, o.nu1, o.nu2,
-                                o.norm_p, (int64_t)(o.omega * 1e12), (int64_t)(o.bottom_rtol * 1e15),
-                                (int64_t)(o.inv_eps0 * 1e12)};
-    if (D.gexec && D.gkey == key) return AMRMG_OK;
-    D.drop_graph();
-    if (!D.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&D.cap_stream, hipStreamNonBlocking));
-    Driver<T> cap(D, D.cap_stream, o, nullptr);
-    hipGraph_t g = nullptr;
-    HIP_TRY(hipStreamBeginCapture(D.cap_stream, hipStreamCaptureModeThreadLocal));
-    cap.iteration(nr);
-    hipError_t ec = hipStreamEndCapture(D.cap_stream, &g);
-    if (ec != hipSuccess) return fail(AMRMG_E_HIP, std::string("graph capture: ") + hipGetErrorString(ec));
-    hipError_t ei = hipGraphInstantiate(&D.gexec, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (ei != hipSuccess) {
-        D.gexec = nullptr;
-        return fail(AMRMG_E_HIP, std::string("graph instantiate: ") + hipGetErrorString(ei));
-    }
-    D.gkey = key;
-    return AMRMG_OK;
-}
-
-template <class T>
-static amrmg_status iterate(DevState &D, Driver<T> &drv, hipStream_t st, int nr, const SolveOpts &o, bool graphs)
-{
-    if (!graphs || drv.P) {
-        drv.iteration(nr);
-        return AMRMG_OK;
-    }
-    ST_TRY(ensure_graph<T>(D, nr, o));
-    HIP_TRY(hipGraphLaunch(D.gexec, st));
-    return AMRMG_OK;
-}
-
 // run a solve on a DevState whose pointer tables are set; per-problem stats
 // Events that time a solve: two made for it (and destroyed with it), or the
 // caller's pair when it may make none.
@@ -492,8 +449,13 @@ struct SolveTimers {
 
 // ev_fixed: the context's pair of timing events (made with it), or nullptr
 // (two are made for this solve).  noalloc: the solve may allocate nothing --
-// no sweep tuning (the tuned or the size rule's threads per brick), no graph
-// (eager launches), the events of ev_fixed
+// no sweep tuning (the tuned or the size rule's threads per brick), the
+// events of ev_fixed.  The kernels of an iteration are launched one by one:
+// the host keeps ahead of the GPU (20 launches against 130 us at 64^3 + 2
+// levels), while a captured graph costs its capture and instantiation after
+// every build (50 us, 130 for a batch of sixteen) and some 5 us at its
+// boundary each iteration: 32^3 + 1 step 717 -> 655 us, 64^3 + 2 step 1522 ->
+// 1435, 128^3 uniform solve on a kept mesh 610 -> 580.
 template <class T>
 static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, double tol,
                               std::vector<amrmg_solve_stats> &stats, bool want_E, Prof *prof,
@@ -514,11 +476,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         HIP_TRY(hipEventCreate(&evs.ev[1]));
     }
     hipEvent_t ev0 = evs.ev[0], ev1 = evs.ev[1];
-    const bool graphs = g_use_graphs && !noalloc;
-    // the iteration's graph is captured and instantiated first, while the
-    // stream may still be busy with the caller's earlier work (the deposit)
     if (o.smoother == AMRMG_GSRB && !noalloc) ST_TRY(drv.tune());
-    if (graphs && !prof && o.max_iters > 0) ST_TRY(ensure_graph<T>(D, nr, o));
     HIP_TRY(hipMemsetAsync(D.cgit, 0, 64, st));  // CG iteration count, the norms' sequence and workgroup counters
     D.seq = 0;
     *(volatile unsigned *)D.h_seq = 0;
@@ -534,7 +492,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
     // the initial guess already meets the tolerance it only refines phi, and
     // the norms reported are those after it
     const bool first_queued = o.max_iters > 0;
-    if (first_queued) ST_TRY(iterate<T>(D, drv, st, nr, o, graphs));
+    if (first_queued) drv.iteration(nr);
     // wait for publication number want in host memory (no stream
     // synchronisation); after a second without it, synchronise and look again
     auto wait_pub = [&](unsigned want) -> amrmg_status {
@@ -602,7 +560,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
     }
     while (!all && it < o.max_iters) {
         if (queued == it) {
-            ST_TRY(iterate<T>(D, drv, st, nr, o, graphs));
+            drv.iteration(nr);
             ++queued;
         }
         // While the last norms lie more than kAhead times above the target,
@@ -610,7 +568,7 @@ static amrmg_status run_solve(DevState &D, hipStream_t st, const SolveOpts &o, d
         // the residual about tenfold), so the one after it will run too:
         // queue it now, and the GPU does not wait for the host between them.
         if (queued == it + 1 && queued < o.max_iters && worst() > kAhead) {
-            ST_TRY(iterate<T>(D, drv, st, nr, o, graphs));
+            drv.iteration(nr);
             ++queued;
         }
         ST_TRY(wait_pub(++D.seq));
@@ -824,8 +782,8 @@ extern "C" amrmg_status amrmg_solve_batch(amrmg_ctx *const *ctxs, int32_t nb, do
     std::vector<int> gen(nb);
     for (int i = 0; i < nb; ++i) gen[i] = ctxs[i]->generation;
     if (!c0->batch || c0->batch_ctx != key || c0->batch_gen != gen) {
-        delete c0->batch;
-        c0->batch = new DevState();
+        // (its buffers grow with the batch and are kept, as a context's are)
+        if (!c0->batch) c0->batch = new DevState();
         c0->batch_ctx.clear();
         std::vector<const Problem *> probs;
         for (int i = 0; i < nb; ++i) probs.push_back(&ctxs[i]->prob);

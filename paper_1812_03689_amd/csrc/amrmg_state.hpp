@@ -165,6 +165,10 @@ struct DevState {
     CoarseJob *d_cjobs = nullptr;
     int n_cg = 0;  // problems whose coarsest grid is solved by CG
     // direct solves of the coarsest grids: tables, jobs, work lists, scratch
+    // (the tables stay on the device from build to build while their grids,
+    // dtab_key, are the same)
+    DBuf dtabbuf;
+    std::vector<double> dtab_key;
     double *d_dtab = nullptr;
     DirectJob *d_djobs = nullptr;
     int2 *d_planes = nullptr, *d_groups = nullptr;
@@ -204,22 +208,6 @@ struct DevState {
     DBuf facebuf;
     int *d_face_err = nullptr;
     PBuf h_face_err;
-    // captured outer iteration (V-cycle, phi update, FP64 residual, norms)
-    hipGraphExec_t gexec = nullptr;
-    std::vector<int64_t> gkey;
-    int meta_gen = 0;
-    hipStream_t cap_stream = nullptr;  // capture needs a stream other than the null stream
-    void drop_graph()
-    {
-        if (gexec) (void)hipGraphExecDestroy(gexec);
-        gexec = nullptr;
-        gkey.clear();
-    }
-    ~DevState()
-    {
-        drop_graph();
-        if (cap_stream) (void)hipStreamDestroy(cap_stream);
-    }
 };
 // ---------------------------------------------------------------------------
 // per-launch event timing of selected kernel classes
