@@ -176,6 +176,11 @@ int hgs_rule_threads(int nb);
 template <class T>
 void launch_hgs(hipStream_t st, const DevMeta &M, int b0, int nb, const T *ein, T *eout, const T *r, T *cp,
                 double *phib, double *ffs, int mode, int nt = 0);
+// the first two sweeps, the first from e = 0, into eout; with face_sums, as
+// HG_FFS; nt as in launch_hgs
+template <class T>
+void launch_hgs_first2(hipStream_t st, const DevMeta &M, int b0, int nb, T *eout, const T *r, double *ffs,
+                       bool face_sums, int nt);
 // direct solve e = A^-1 r of the coarsest grids of the listed jobs: planes
 // (job, z | x-block << 8) for the x/y transforms, column groups (job, first
 // column) for the z transform; FP64 scratch W; phi += e on AMR grids when

@@ -316,14 +316,19 @@ struct Driver {
     {
         int b0 = step_b0(k), nb = step_nb(k);
         const double n = (double)nb * BRICK_CELLS;
-        T *out = (o.nu1 % 2 == 1) ? e : et;
         // the last pre-smoothing sweep also writes the fine sums of e that the
-        // restriction's coarse-fine update reads
+        // restriction's coarse-fine update reads; the result ends in e
+        int done = o.nu1 >= 2 ? 2 : 1;
+        T *src = (o.nu1 - done) % 2 ? et : e;
         pb(AMRMG_K_GSRB);
-        launch_hgs<T>(st, D.M, b0, nb, nullptr, out, r, nullptr, D.phib, D.ffs, o.nu1 <= 1 ? 1 | 16 : 1, hgs_nt(k));
+        if (done == 2) {
+            launch_hgs_first2<T>(st, D.M, b0, nb, src, r, D.ffs, o.nu1 == 2, hgs_nt(k));
+        } else {
+            src = e;
+            launch_hgs<T>(st, D.M, b0, nb, nullptr, src, r, nullptr, D.phib, D.ffs, 1 | 16, hgs_nt(k));
+        }
         pe(AMRMG_K_GSRB, 2.0 * n * W);
-        T *src = out;
-        for (int i = 1; i < o.nu1; ++i) {
+        for (int i = done; i < o.nu1; ++i) {
             T *dst = (src == e) ? et : e;
             pb(AMRMG_K_GSRB);
             launch_hgs<T>(st, D.M, b0, nb, src, dst, r, nullptr, D.phib, D.ffs, i == o.nu1 - 1 ? 16 : 0, hgs_nt(k));
