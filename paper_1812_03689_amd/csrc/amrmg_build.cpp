@@ -336,7 +336,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         };
         const size_t o_pool = at(4 * (size_t)npool), o_org = at(16 * nbp), o_ub = at(8 * nbp), o_us = at(8 * nbp),
                      o_ch = at(32 * nbp), o_par = at(4 * nbp), o_nbr = at(24 * nbp), o_gfo = at(24 * nbp),
-                     o_rf = at(4 * nbp), o_amr = at(4 * nbp), o_cm = at(nbp), o_cnt = at(8 * nbp),
+                     o_rf = at(4 * nbp), o_amr = at(4 * nbp), o_cm = at(nbp), o_er = at(nbp), o_cnt = at(8 * nbp),
                      o_off = at(8 * nbp), o_flag = at(4 * nbp), o_roff = at(4 * nbp), o_dof = at(8 * (size_t)nent),
                      o_err = at(4), o_tmp = at(B.temp_bytes);
         HIP_TRY(D.brickbuf.ensure(o));
@@ -352,6 +352,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         B.reflux = (int32_t *)(p + o_rf);
         B.amr_list = (int32_t *)(p + o_amr);
         B.cmask = (uint8_t *)(p + o_cm);
+        B.eread = (uint8_t *)(p + o_er);
         B.cnt = (uint64_t *)(p + o_cnt);
         B.off = (uint64_t *)(p + o_off);
         B.flag = (uint32_t *)(p + o_flag);
@@ -417,6 +418,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.M.child = B.child;
     D.M.par = B.par;
     D.M.cmask = B.cmask;
+    D.M.eread = B.eread;
     D.M.ubase = B.ubase;
     D.M.ustr = B.ustr;
     D.M.gf_owner = B.gf_owner;
@@ -431,7 +433,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.d_jobs = (int4 *)dj;
     int32_t *dpool = B.pool;
     HIP_TRY(hipMemsetAsync(D.d_face_err, 0, sizeof(int), st));
-    launch_face_data(st, D.M, dent, dpool, dmono, gbc, cfp, cfi, D.d_face_err);
+    launch_face_data(st, D.M, dent, dpool, dmono, gbc, cfp, cfi, B.eread, D.d_face_err);
     HIP_TRY(hipGetLastError());
     *(int *)D.h_face_err.p = 0;
     HIP_TRY(hipMemcpyAsync(D.h_face_err.p, D.d_face_err, sizeof(int), hipMemcpyDeviceToHost, st));

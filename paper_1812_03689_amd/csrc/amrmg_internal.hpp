@@ -38,6 +38,7 @@ struct DevMeta {
     const int32_t *child;     // [nbrick*8] child brick per octant or -1
     const int32_t *par;       // [nbrick] (parent brick << 3 | octant) or -1
     const uint8_t *cmask;     // [nbrick] covered-octant mask
+    const uint8_t *eread;     // [nbrick] AMR bricks: 1 when the finer level reads the brick's values
     const int64_t *ubase;     // [nbrick] user-layout index of the brick's (0,0,0) cell
     const int2 *ustr;         // [nbrick] user-layout strides (y, z)
     const int32_t *gf_owner;  // [ngface] brick << 3 | face

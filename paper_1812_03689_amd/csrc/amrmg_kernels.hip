@@ -916,7 +916,9 @@ struct SrcProl {
 // MODE bits: 1 input is zero; 2 input plus the parent correction (fused
 // prolongation); 4 coarse parts of the coarse-fine ghosts computed from the
 // coarse level's values in ein and stored into cp (else read from cp);
-// 8 phi += result on AMR bricks (fused phi update; phi in brick layout);
+// 8 phi += result on AMR bricks (fused phi update; phi in brick layout), the
+// result itself stored only where the finer level reads it (1.9e8 cells 1050
+// -> 891 us, 2.7e7 147 -> 128);
 // 16 the fine sums of the result on the brick's coarse-fine faces into ffs.
 enum { HG_ZERO = 1, HG_PROL = 2, HG_CPIN = 4, HG_PHI = 8, HG_FFS = 16 };
 
@@ -1012,7 +1014,8 @@ __global__ void __launch_bounds__(64 * BPW) k_hgs(DevMeta M, int b0, int nb, con
         if (MODE & HG_CPIN) return (T)CpInline<T>{&M, ein, active ? cp : nullptr}(cf, fl);
         return cp ? cp[cf * 64 + fl] : (T)0;
     };
-    // every load first: right-hand sides, input, halo slots
+    const LevelConst L = M.lc[M.org[b].w];
+    // every load first: right-hand sides, input, halo slots, phi
     const size_t rb = (size_t)b * BRICK_CELLS + 8 * lane;
     T rr[8], er[8], hs[6];
     Row8<T>::load(r + rb, rr);
@@ -1039,7 +1042,9 @@ __global__ void __launch_bounds__(64 * BPW) k_hgs(DevMeta M, int b0, int nb, con
     const bool lx_p = BPW > 1 && w + 1 < BPW && k0 + 1 < nb && kind[1] == 0 && nbf[1] == b + 1;
 #pragma unroll
     for (int f = 0; f < 6; ++f) hs[f] = (f == 0 && lx_m) || (f == 1 && lx_p) ? (T)0 : slot(f, lane);
-    const LevelConst L = M.lc[M.org[b].w];
+    const bool phi = (MODE & HG_PHI) && L.amr >= 0;
+    double ph[8];
+    if (phi) Row8<double>::load(phib + rb, ph);
     const T ih2x = (T)L.ih2[0], ih2y = (T)L.ih2[1], ih2z = (T)L.ih2[2];
     const int rym = rrow(y - 1, z), ryp = rrow(y + 1, z), rzm = rrow(y, z - 1), rzp = rrow(y, z + 1), rme = rrow(y, z);
 #pragma unroll
@@ -1102,10 +1107,10 @@ __global__ void __launch_bounds__(64 * BPW) k_hgs(DevMeta M, int b0, int nb, con
         __syncthreads();
     }
     if (!active) return;
-    Row8<T>::store(eout + rb, er);
-    if ((MODE & HG_PHI) && L.amr >= 0) {
-        double ph[8];
-        Row8<double>::load(phib + rb, ph);
+    // the last sweep's result is read again only where the finer level is
+    // (parents and interpolation windows)
+    if (!phi || M.eread[b]) Row8<T>::store(eout + rb, er);
+    if (phi) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) ph[i] += (double)er[i];
         Row8<double>::store(phib + rb, ph);

@@ -73,7 +73,7 @@ struct MetaBuild {
     int64_t *ubase;
     int2 *ustr;
     int32_t *child, *par, *nbr, *gf_owner, *reflux, *amr_list;
-    uint8_t *cmask;
+    uint8_t *cmask, *eread;
     uint64_t *cnt, *off;      // [nbrick + 1]
     uint32_t *flag, *roff;    // [nbrick + 1]
     unsigned long long *dof;  // [nent]
@@ -96,9 +96,10 @@ size_t meta_scan_temp_bytes(int nbrick);
 hipError_t launch_meta_build(hipStream_t st, const MetaBuild &B);
 // Dirichlet values of the boundary faces (gbc) and the coarse-fine windows
 // (cf_pat, cf_idx) of the hierarchy in M; *err is set when a window leaves
-// the coarser level
+// the coarser level.  eread (marked by launch_meta_build where a brick has
+// children) also gets the bricks of the windows
 void launch_face_data(hipStream_t st, const DevMeta &M, const EntryDev *ent, const int32_t *pool,
-                      const double *mono, double *gbc, uint8_t *cf_pat, int32_t *cf_idx, int *err);
+                      const double *mono, double *gbc, uint8_t *cf_pat, int32_t *cf_idx, uint8_t *eread, int *err);
 // the next kernel launched by a launcher records kernel-execution timestamps
 // into these events (hipExtLaunchKernelGGL); cleared after that launch
 void set_launch_timing(hipEvent_t start, hipEvent_t stop);

@@ -48,7 +48,7 @@ __device__ __forceinline__ int brick_of(const EntryDev &E, const int32_t *pool, 
 // flight together, and bit masks (14.8 -> 7.0 us a build; cell by cell, two
 // lookups each after the other, the chain was 50 loads long).
 __global__ void __launch_bounds__(256) k_cf_windows(DevMeta M, const EntryDev *ent, const int32_t *pool,
-                                                    uint8_t *cf_pat, int32_t *cf_idx, int *err)
+                                                    uint8_t *cf_pat, int32_t *cf_idx, uint8_t *eread, int *err)
 {
     int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= M.ncf * 16) return;
@@ -120,10 +120,12 @@ __global__ void __launch_bounds__(256) k_cf_windows(DevMeta M, const EntryDev *e
             P[du] = cu + ou;
             P[dv] = cv + ov;
             int gi = 0;
-            if (q < 0)
+            if (q < 0) {
                 *err = 1;  // the window leaves the coarser level: nesting is violated
-            else
+            } else {
+                eread[q] = 1;
                 gi = q * BRICK_CELLS + (P[0] & 7) + 8 * (P[1] & 7) + 64 * (P[2] & 7);
+            }
             cf_idx[(size_t)i * 9 + a + 3 * b] = gi;
         }
 }
@@ -270,7 +272,7 @@ __global__ void __launch_bounds__(256) k_meta_links(int nbrick, const EntryDev *
 
 __global__ void __launch_bounds__(256) k_meta_faces(int nbrick, const EntryDev *ent, const int4 *org,
                                                     const uint64_t *off, int32_t *nbr, int32_t *gf_owner,
-                                                    const int32_t *child, uint8_t *cmask)
+                                                    const int32_t *child, uint8_t *cmask, uint8_t *eread)
 {
     const int g = blockIdx.x * 256 + threadIdx.x;
     if (g >= nbrick) return;
@@ -290,6 +292,7 @@ __global__ void __launch_bounds__(256) k_meta_faces(int nbrick, const EntryDev *
 #pragma unroll
         for (int o = 0; o < 8; ++o) cm |= (child[(size_t)g * 8 + o] >= 0 ? 1u : 0u) << o;
     cmask[g] = (uint8_t)cm;
+    eread[g] = cm != 0;
 }
 
 __global__ void __launch_bounds__(256) k_meta_reflux(int nbrick, const EntryDev *ent, const int4 *org,
@@ -404,7 +407,7 @@ hipError_t launch_meta_build(hipStream_t st, const MetaBuild &B)
     e = exclusive_scan<uint64_t>(st, B.cnt, B.off, B.nbrick + 1, B.temp, B.temp_bytes);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_meta_faces, dim3(g1), dim3(256), 0, st, B.nbrick, B.ent, B.org, B.off, B.nbr, B.gf_owner,
-                       B.child, B.cmask);
+                       B.child, B.cmask, B.eread);
     hipLaunchKernelGGL(k_meta_reflux, dim3(g1), dim3(256), 0, st, B.nbrick, B.ent, B.org, B.nbr, B.cmask, B.flag,
                        B.dof, B.amr_list);
     e = exclusive_scan<uint32_t>(st, B.flag, B.roff, B.nbrick + 1, B.temp, B.temp_bytes);
@@ -415,13 +418,13 @@ hipError_t launch_meta_build(hipStream_t st, const MetaBuild &B)
 }
 
 void launch_face_data(hipStream_t st, const DevMeta &M, const EntryDev *ent, const int32_t *pool,
-                      const double *mono, double *gbc, uint8_t *cf_pat, int32_t *cf_idx, int *err)
+                      const double *mono, double *gbc, uint8_t *cf_pat, int32_t *cf_idx, uint8_t *eread, int *err)
 {
     if (M.nbc > 0)
         hipLaunchKernelGGL(k_bc_values, dim3((M.nbc * 64 + 255) / 256), dim3(256), 0, st, M, ent, mono, gbc);
     if (M.ncf > 0)
         hipLaunchKernelGGL(k_cf_windows, dim3((M.ncf * 16 + 255) / 256), dim3(256), 0, st, M, ent, pool, cf_pat,
-                           cf_idx, err);
+                           cf_idx, eread, err);
 }
 
 }  // namespace amrmg
