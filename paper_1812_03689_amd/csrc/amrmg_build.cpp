@@ -402,17 +402,15 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.d_amr = B.amr_list;
     D.d_bmap.assign(amr_off.size(), nullptr);
     for (size_t l = 0; l < amr_off.size(); ++l) D.d_bmap[l] = B.pool + amr_off[l];
-    // face data buffers: gbc [nbc*64], cf_idx [ncf*144], cf_pat [ncf*16], error flag
+    // face data buffers: gbc [nbc*64], cf_idx [ncf*144], cf_pat [ncf*16]
     size_t o_gbc = 0, o_idx = align256((size_t)m.nbc * 64 * 8 + 8);
     size_t o_pat = o_idx + align256((size_t)m.ncf * 144 * 4 + 4);
-    size_t o_err = o_pat + align256((size_t)m.ncf * 16 + 1);
-    HIP_TRY(D.facebuf.ensure(o_err + 256));
+    HIP_TRY(D.facebuf.ensure(o_pat + align256((size_t)m.ncf * 16 + 1)));
     HIP_TRY(D.h_face_err.ensure(sizeof(int)));
     char *fb = (char *)D.facebuf.p;
     gbc = (double *)(fb + o_gbc);
     cfi = (int32_t *)(fb + o_idx);
     cfp = (uint8_t *)(fb + o_pat);
-    D.d_face_err = (int *)(fb + o_err);
     D.M.org = B.org;
     D.M.nbr = B.nbr;
     D.M.child = B.child;
@@ -432,11 +430,12 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.norms.first = dnf;
     D.d_jobs = (int4 *)dj;
     int32_t *dpool = B.pool;
-    HIP_TRY(hipMemsetAsync(D.d_face_err, 0, sizeof(int), st));
-    launch_face_data(st, D.M, dent, dpool, dmono, gbc, cfp, cfi, B.eread, D.d_face_err);
-    HIP_TRY(hipGetLastError());
+    // the error flag in pinned host memory, written by the kernel where there
+    // is an error (what came before in the stream is done: the counts above
+    // have arrived)
     *(int *)D.h_face_err.p = 0;
-    HIP_TRY(hipMemcpyAsync(D.h_face_err.p, D.d_face_err, sizeof(int), hipMemcpyDeviceToHost, st));
+    launch_face_data(st, D.M, dent, dpool, dmono, gbc, cfp, cfi, B.eread, (int *)D.h_face_err.p);
+    HIP_TRY(hipGetLastError());
     // per-level pointer tables (filled per call)
     size_t ne = m.ent.size();
     D.h_phi.assign(ne, nullptr);
@@ -459,7 +458,8 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
 
 // Geometry of the tagging passes on level L: per brick its origin, its
 // caller's-layout base and strides, and the level's brick map, uploaded to
-// the device; the block marks of level l+1 cleared.
+// the device; the block marks of level l+1, rho (the level's charge) and
+// the count nout cleared where given.
 struct TagGeom {
     int32_t *borg = nullptr, *us = nullptr, *bmap = nullptr;
     int64_t *ub = nullptr;
@@ -469,7 +469,8 @@ struct TagGeom {
     size_t ng = 0;
 };
 
-static amrmg_status tag_geometry(amrmg_ctx *ctx, const HostLevel &L, TagGeom &G)
+static amrmg_status tag_geometry(amrmg_ctx *ctx, const HostLevel &L, TagGeom &G, double *rho = nullptr,
+                                 unsigned long long *nout = nullptr)
 {
     const amrmg_params &P = ctx->P;
     hipStream_t st = ctx->st;
@@ -502,8 +503,9 @@ static amrmg_status tag_geometry(amrmg_ctx *ctx, const HostLevel &L, TagGeom &G)
     G.g = make_int3(2 * L.n[0] / P.blocking_factor, 2 * L.n[1] / P.blocking_factor, 2 * L.n[2] / P.blocking_factor);
     G.ng = (size_t)G.g.x * G.g.y * G.g.z;
     HIP_TRY(ctx->tag_scratch.ensure(sizeof(double) * 1040));
-    HIP_TRY(ctx->tag_marks.ensure(G.ng));
-    HIP_TRY(hipMemsetAsync(ctx->tag_marks.p, 0, G.ng, st));
+    const size_t mw = (G.ng + 7) / 8;  // marks in whole words
+    HIP_TRY(ctx->tag_marks.ensure(8 * mw));
+    launch_clear(st, rho, rho ? G.nc : 0, (uint64_t *)ctx->tag_marks.p, (int64_t)mw, nout);
     return AMRMG_OK;
 }
 
@@ -522,12 +524,12 @@ static amrmg_status tag_boxes(amrmg_ctx *ctx, const HostLevel &L, const TagGeom 
 {
     const amrmg_params &P = ctx->P;
     const size_t nw = (G.ng + 63) / 64;
-    HIP_TRY(ctx->tag_bits.ensure(8 * nw));
     HIP_TRY(ctx->tag_host.ensure(8 * nw));
+    // the kernel writes the words to pinned host memory (a build with a copy
+    // after it instead: 4 us more tagging 128^3 cells, 10 tagging 384^3)
     launch_nest_pack(ctx->st, (const uint8_t *)ctx->tag_marks.p, (int64_t)G.ng, G.g, G.bmap,
                      make_int3(L.n[0], L.n[1], L.n[2]), make_int3(L.nbk[0], L.nbk[1], L.nbk[2]),
-                     P.blocking_factor / 2, P.n_proper, (uint64_t *)ctx->tag_bits.p);
-    HIP_TRY(hipMemcpyAsync(ctx->tag_host.p, ctx->tag_bits.p, 8 * nw, hipMemcpyDeviceToHost, ctx->st));
+                     P.blocking_factor / 2, P.n_proper, (uint64_t *)ctx->tag_host.p);
     HIP_TRY(hipStreamSynchronize(ctx->st));
     HIP_TRY(hipGetLastError());
     const int g[3] = {G.g.x, G.g.y, G.g.z};
@@ -545,11 +547,10 @@ static amrmg_status tag_level(amrmg_ctx *ctx, const HostLevel &L, int pos_dtype,
 {
     hipStream_t st = ctx->st;
     TagGeom G;
-    ST_TRY(tag_geometry(ctx, L, G));
     // the level's charge is kept for amrmg_deposit_built
-    HIP_TRY(ctx->lev_rho[L.amr].ensure(sizeof(double) * G.nc));
+    HIP_TRY(ctx->lev_rho[L.amr].ensure(sizeof(double) * L.ncells()));
     double *rho = (double *)ctx->lev_rho[L.amr].p;
-    launch_fill(st, rho, G.nc, 0.0);
+    ST_TRY(tag_geometry(ctx, L, G, rho, nout));
     Problem &pr = ctx->prob;
     DepArgs A{};
     A.nlev = 1;
@@ -611,7 +612,7 @@ static amrmg_status tag_level_field(amrmg_ctx *ctx, int l, int pos_dtype, const 
         if (field)
             for (int d = 0; d < 3; ++d, cur += nc) E[3 * k + d] = cur;
     }
-    launch_fill(st, (double *)ctx->tag_fields.p, nv * total, 0.0);
+    launch_clear(st, (double *)ctx->tag_fields.p, nv * total, nullptr, 0, nullptr);
     rc = amrmg_deposit(ctx, pos_dtype, x, y, z, q, n, rho.data(), nullptr);
     if (rc == AMRMG_OK)
         rc = amrmg_solve(ctx, rho.data(), phi.data(), field ? E.data() : nullptr, AMRMG_TAG_SOLVE_TOL, nullptr);
@@ -671,7 +672,6 @@ extern "C" amrmg_status amrmg_build_hierarchy(amrmg_ctx *ctx, int pos_dtype, con
         copy_done = true;
     };
     HIP_TRY(ctx->built_nout.ensure(sizeof(unsigned long long)));
-    HIP_TRY(hipMemsetAsync(ctx->built_nout.p, 0, sizeof(unsigned long long), ctx->st));
     const uint32_t *tperm = nullptr;
 
     Problem &pr = ctx->prob;

@@ -2785,15 +2785,21 @@ __global__ void __launch_bounds__(256) k_copy(const T *a, T *b, int64_t n)
 // Tag cells of one level (|rho| > lambda * max|rho|) and mark the blocks of
 // the finer level (bf fine cells = half coarse cells per edge) that a tag
 // dilated by nbuf cells reaches.  Same value written by every marker.
+// max|rho| comes from the partial maxima of k_absmax_part (at most 1024), by
+// each workgroup for itself: a launch between the two for one number cost
+// more than the reads (2.0 us and a launch, twice a build of three levels).
 __global__ void __launch_bounds__(256) k_mark_blocks(const double *rho, const int4 *borg, const int64_t *ubase,
-                                                     const int2 *ustr, int nb, const double *vmax, double lambda,
-                                                     int nbuf, int half, int3 n, int3 g, uint8_t *marks)
+                                                     const int2 *ustr, int nb, const double *part, int parts,
+                                                     double lambda, int nbuf, int half, int3 n, int3 g, uint8_t *marks)
 {
     int b = xcd_remap(blockIdx.x, nb);
+    double vmax = 0.0;
+    for (int i = threadIdx.x; i < parts; i += 256) vmax = fmax(vmax, part[i]);
+    vmax = block_reduce(vmax, 1);
     int4 o = borg[b];
     int64_t ub = ubase[b];
     int2 us = ustr[b];
-    double thr = lambda * (*vmax);
+    double thr = lambda * vmax;
     for (int c = threadIdx.x; c < BRICK_CELLS; c += 256) {
         int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
         double v = rho[ub + x + (int64_t)us.x * y + (int64_t)us.y * z];
@@ -2808,18 +2814,19 @@ __global__ void __launch_bounds__(256) k_mark_blocks(const double *rho, const in
     }
 }
 
-__global__ void __launch_bounds__(256) k_fill_multi(DepArgs A, int64_t total, const int64_t *dummy)
+// Every level's dst from its src, or zero without one, and a counter cleared:
+// one launch for all levels (a copy or a fill of a small one is all launch).
+__global__ void __launch_bounds__(256) k_set_levels(LevelSet A, unsigned long long *count)
 {
-    (void)dummy;
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0 && count) *count = 0;
     for (int l = 0; l < A.nlev; ++l) {
         if (i < A.ncell[l]) {
-            A.rho[l][i] = 0.0;
+            A.dst[l][i] = A.src[l] ? A.src[l][i] : 0.0;
             return;
         }
         i -= A.ncell[l];
     }
-    (void)total;
 }
 
 // Proper nesting of the marked blocks of the finer level: a block stays
@@ -2853,10 +2860,14 @@ __global__ void __launch_bounds__(256) k_nest_pack(const uint8_t *marks, int64_t
     if ((threadIdx.x & 63) == 0 && t < total) bits[t >> 6] = m;
 }
 
-__global__ void __launch_bounds__(256) k_fill(double *v, int64_t n, double val)
+// v [n], w [nw] and a counter cleared, in one launch
+__global__ void __launch_bounds__(256) k_clear(double *v, int64_t n, uint64_t *w, int64_t nw,
+                                               unsigned long long *count)
 {
     int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) v[i] = val;
+    if (i < n) v[i] = 0.0;
+    if (i < nw) w[i] = 0;
+    if (i == 0 && count) *count = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -3189,24 +3200,24 @@ void launch_mark_blocks(hipStream_t st, const double *rho, int64_t ncell, const 
     if (nb <= 0) return;
     int parts = (int)blocks_for(ncell, 256);
     if (parts > 1024) parts = 1024;
-    AMRMG_LAUNCH(k_absmax_part, dim3(parts), dim3(256), 0, st, rho, ncell, scratch + 1);
-    AMRMG_LAUNCH(k_absmax_final, dim3(1), dim3(256), 0, st, scratch + 1, parts, scratch);
-    AMRMG_LAUNCH(k_mark_blocks, dim3(nb), dim3(256), 0, st, rho, borg, ubase, ustr, nb, scratch, lambda, nbuf,
-                       half, n, g, marks);
+    AMRMG_LAUNCH(k_absmax_part, dim3(parts), dim3(256), 0, st, rho, ncell, scratch);
+    AMRMG_LAUNCH(k_mark_blocks, dim3(nb), dim3(256), 0, st, rho, borg, ubase, ustr, nb, scratch, parts, lambda, nbuf,
+                 half, n, g, marks);
 }
 
-void launch_zero_levels(hipStream_t st, const DepArgs &A)
+void launch_set_levels(hipStream_t st, const LevelSet &A, unsigned long long *count)
 {
     int64_t total = 0;
     for (int l = 0; l < A.nlev; ++l) total += A.ncell[l];
-    if (total <= 0) return;
-    hipLaunchKernelGGL(k_fill_multi, dim3(blocks_for(total, 256)), dim3(256), 0, st, A, total, nullptr);
+    if (total <= 0) total = 1;  // the counter
+    hipLaunchKernelGGL(k_set_levels, dim3(blocks_for(total, 256)), dim3(256), 0, st, A, count);
 }
 
-void launch_fill(hipStream_t st, double *v, int64_t n, double val)
+void launch_clear(hipStream_t st, double *v, int64_t n, uint64_t *w, int64_t nw, unsigned long long *count)
 {
-    if (n <= 0) return;
-    AMRMG_LAUNCH(k_fill, dim3(blocks_for(n, 256)), dim3(256), 0, st, v, n, val);
+    int64_t total = n > nw ? n : nw;
+    if (total <= 0) total = 1;  // the counter
+    hipLaunchKernelGGL(k_clear, dim3(blocks_for(total, 256)), dim3(256), 0, st, v, n, w, nw, count);
 }
 
 #define AMRMG_INST(T)                                                                                            \

@@ -26,6 +26,13 @@ struct DepArgs {
     int nlev;
 };
 
+struct LevelSet {
+    double *dst[MAX_AMR];
+    const double *src[MAX_AMR];
+    int64_t ncell[MAX_AMR];
+    int nlev;
+};
+
 struct GatherArgs {
     DepLevel lev[MAX_AMR];
     int nlev;
@@ -209,7 +216,10 @@ void launch_deposit(hipStream_t st, int pos_f32, int64_t n, const void *x, const
 // rec[i] = (x, y, z, q) of particle i (q 0 when it is nullptr)
 void launch_pack_records(hipStream_t st, int pos_f32, int64_t n, const void *x, const void *y, const void *z,
                          const double *q, double4 *rec);
-void launch_zero_levels(hipStream_t st, const DepArgs &A);
+// dst[l] = src[l] (zero where it is nullptr) on every level; *count = 0 when given
+void launch_set_levels(hipStream_t st, const LevelSet &A, unsigned long long *count);
+// v [n] and w [nw] to zero; *count = 0 when given
+void launch_clear(hipStream_t st, double *v, int64_t n, uint64_t *w, int64_t nw, unsigned long long *count);
 // ordered: x, y, z are already in the order perm gives (x[i] is particle
 // perm[i], the build's ordered copy); E is written at perm[i].  With perm,
 // its inverse iperm and out ([n] staging records), E goes to out in the
@@ -223,7 +233,6 @@ void launch_gather(hipStream_t st, int pos_f32, int64_t n, const void *x, const 
                    const int64_t *ubase, const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out,
                    bool ordered = false, bool tile = false);
 void launch_tag(hipStream_t st, const double *v, int64_t n, double lambda, double *scratch, uint8_t *tags);
-void launch_fill(hipStream_t st, double *v, int64_t n, double val);
 // spatial visiting order of the particles (stable radix sort by the
 // Morton code of their cell on a sort grid: the level-0 grid n0 refined
 // towards about four particles per cell but at most levels times, at most

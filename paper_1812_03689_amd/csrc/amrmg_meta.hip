@@ -47,10 +47,9 @@ __device__ __forceinline__ int brick_of(const EntryDev &E, const int32_t *pool, 
 // bricks (four coarse cells wide) per axis of the face: eight lookups, all in
 // flight together, and bit masks (14.8 -> 7.0 us a build; cell by cell, two
 // lookups each after the other, the chain was 50 loads long).
-__global__ void __launch_bounds__(256) k_cf_windows(DevMeta M, const EntryDev *ent, const int32_t *pool,
-                                                    uint8_t *cf_pat, int32_t *cf_idx, uint8_t *eread, int *err)
+__device__ void cf_windows(int i, const DevMeta &M, const EntryDev *ent, const int32_t *pool, uint8_t *cf_pat,
+                           int32_t *cf_idx, uint8_t *eread, int *err)
 {
-    int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= M.ncf * 16) return;
     int t = i >> 4, m = i & 15;
     int ow = M.gf_owner[M.nbc + t];
@@ -133,9 +132,8 @@ __global__ void __launch_bounds__(256) k_cf_windows(DevMeta M, const EntryDev *e
 // One thread per (boundary face, face cell): the Dirichlet value of the sum
 // of the problem's monopoles q / (4 pi eps0 |x - x_m|) at the face centre;
 // zero below AMR level 0 (the correction equation there is homogeneous).
-__global__ void __launch_bounds__(256) k_bc_values(DevMeta M, const EntryDev *ent, const double *mono, double *gbc)
+__device__ void bc_values(int i, const DevMeta &M, const EntryDev *ent, const double *mono, double *gbc)
 {
-    int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= M.nbc * 64) return;
     int t = i >> 6, f = i & 63;
     int ow = M.gf_owner[t];
@@ -162,6 +160,17 @@ __global__ void __launch_bounds__(256) k_bc_values(DevMeta M, const EntryDev *en
         }
     }
     gbc[i] = v;
+}
+
+// Both, independent of each other and short, in one launch: the first ncfw
+// workgroups the windows (the longer chain), the others the boundary values.
+__global__ void __launch_bounds__(256) k_face_data(DevMeta M, const EntryDev *ent, const int32_t *pool, int ncfw,
+                                                   const double *mono, double *gbc, uint8_t *cf_pat,
+                                                   int32_t *cf_idx, uint8_t *eread, int *err)
+{
+    const int wg = blockIdx.x;
+    if (wg < ncfw) cf_windows(wg * 256 + threadIdx.x, M, ent, pool, cf_pat, cf_idx, eread, err);
+    else bc_values((wg - ncfw) * 256 + threadIdx.x, M, ent, mono, gbc);
 }
 
 // ---------------------------------------------------------------------------
@@ -420,10 +429,9 @@ hipError_t launch_meta_build(hipStream_t st, const MetaBuild &B)
 void launch_face_data(hipStream_t st, const DevMeta &M, const EntryDev *ent, const int32_t *pool,
                       const double *mono, double *gbc, uint8_t *cf_pat, int32_t *cf_idx, uint8_t *eread, int *err)
 {
-    if (M.nbc > 0)
-        hipLaunchKernelGGL(k_bc_values, dim3((M.nbc * 64 + 255) / 256), dim3(256), 0, st, M, ent, mono, gbc);
-    if (M.ncf > 0)
-        hipLaunchKernelGGL(k_cf_windows, dim3((M.ncf * 16 + 255) / 256), dim3(256), 0, st, M, ent, pool, cf_pat,
+    const int ncfw = (M.ncf * 16 + 255) / 256, nbcw = (M.nbc * 64 + 255) / 256;
+    if (ncfw + nbcw > 0)
+        hipLaunchKernelGGL(k_face_data, dim3(ncfw + nbcw), dim3(256), 0, st, M, ent, pool, ncfw, mono, gbc, cf_pat,
                            cf_idx, eread, err);
 }
 

@@ -128,18 +128,18 @@ extern "C" amrmg_status amrmg_deposit(amrmg_ctx *ctx, int pos_dtype, const void 
     if (n_outside) {
         HIP_TRY(ctx->dep_count.ensure(sizeof(unsigned long long)));
         dout = (unsigned long long *)ctx->dep_count.p;
-        HIP_TRY(hipMemsetAsync(dout, 0, sizeof(unsigned long long), ctx->st));
     }
     DepArgs A{};
-    A.nlev = pr.namr();
+    LevelSet S{};
+    A.nlev = S.nlev = pr.namr();
     for (int l = 0; l < pr.namr(); ++l) {
         if (!rho[l]) return fail(AMRMG_E_INVALID, "rho[l] is NULL");
         const HostLevel &L = pr.lev[pr.kg + l];
         A.lev[l] = dep_level(pr, L, ctx->ds.d_bmap[l]);
-        A.rho[l] = rho[l];
-        A.ncell[l] = L.ncells();
+        A.rho[l] = S.dst[l] = rho[l];
+        A.ncell[l] = S.ncell[l] = L.ncells();
     }
-    launch_zero_levels(ctx->st, A);
+    launch_set_levels(ctx->st, S, dout);
     int64_t cells = 0;
     for (int l = 0; l < A.nlev; ++l) cells += A.ncell[l];
     const double4 *rec = moved_records(ctx, pos_dtype, x, y, z, q, n);
@@ -170,13 +170,16 @@ extern "C" amrmg_status amrmg_deposit_built(amrmg_ctx *ctx, double *const *rho, 
     // levels deposited by the build are copied; the others are deposited
     // together from the ordered copy (positions after the charges)
     DepArgs A{};
+    LevelSet S{};
+    S.nlev = pr.namr();
     int finest = 0;
     for (int l = 0; l < pr.namr(); ++l) {
         if (!rho[l]) return fail(AMRMG_E_INVALID, "rho[l] is NULL");
         const HostLevel &L = pr.lev[pr.kg + l];
+        S.dst[l] = rho[l];
+        S.ncell[l] = L.ncells();
         if (l < (int)ctx->lev_rho_ok.size() && ctx->lev_rho_ok[l]) {
-            HIP_TRY(hipMemcpyAsync(rho[l], ctx->lev_rho[l].p, sizeof(double) * L.ncells(), hipMemcpyDeviceToDevice,
-                                   ctx->st));
+            S.src[l] = (const double *)ctx->lev_rho[l].p;
             continue;
         }
         finest = l;
@@ -187,13 +190,12 @@ extern "C" amrmg_status amrmg_deposit_built(amrmg_ctx *ctx, double *const *rho, 
     }
     unsigned long long *dout = nullptr;
     const bool level0_kept = !ctx->lev_rho_ok.empty() && ctx->lev_rho_ok[0];
+    if (n_outside && !level0_kept) {
+        HIP_TRY(ctx->dep_count.ensure(sizeof(unsigned long long)));
+        dout = (unsigned long long *)ctx->dep_count.p;
+    }
+    launch_set_levels(ctx->st, S, dout);
     if (A.nlev > 0) {
-        launch_zero_levels(ctx->st, A);
-        if (n_outside && !level0_kept) {
-            HIP_TRY(ctx->dep_count.ensure(sizeof(unsigned long long)));
-            dout = (unsigned long long *)ctx->dep_count.p;
-            HIP_TRY(hipMemsetAsync(dout, 0, sizeof(unsigned long long), ctx->st));
-        }
         const size_t ps = pos == AMRMG_POS_F32 ? 4 : 8;
         const char *base = (const char *)ctx->sorted.p;
         const double *qs = (const double *)base;

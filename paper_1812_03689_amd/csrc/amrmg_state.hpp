@@ -206,7 +206,6 @@ struct DevState {
     std::vector<int32_t *> d_bmap;
     // face data generated on the device: gbc, cf_pat, cf_idx, error flag
     DBuf facebuf;
-    int *d_face_err = nullptr;
     PBuf h_face_err;
 };
 // ---------------------------------------------------------------------------
@@ -297,7 +296,7 @@ struct amrmg_ctx {
     bool built = false;
     DevState ds;
     // scratch of the tagging passes of build_hierarchy
-    DBuf tag_marks, tag_scratch, tag_geom, tag_fields, tag_bits;
+    DBuf tag_marks, tag_scratch, tag_geom, tag_fields;
     PBuf tag_stage, tag_host;
     // spatial visiting order of the particles (a performance hint for the
     // deposit; any order gives the same sums up to rounding)
