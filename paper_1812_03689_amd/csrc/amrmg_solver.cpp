@@ -347,9 +347,11 @@ struct Driver {
             int mode = (i == 0 ? 2 | 4 : 0) | (i == o.nu2 - 1 ? 8 : 0);
             pb(AMRMG_K_GSRB);
             launch_hgs<T>(st, D.M, b0, nb, src, dst, r, cpe, D.phib, D.ffs, mode, hgs_nt(k));
-            // e, r in; e out; the parent value with the fused prolongation;
-            // phi read and written on AMR bricks with the fused update
-            pe(AMRMG_K_GSRB, (3.0 + (i == 0 ? 0.125 : 0.0)) * n * W + ((mode & 8) ? 16.0 * step_amr_cells(k) : 0.0));
+            // e, r in; e out (not from the finest level's last sweep); the
+            // parent value with the fused prolongation; phi read and written
+            // on AMR bricks with the fused update
+            const double we = (mode & 8) && k == m.K - 1 ? 2.0 : 3.0;
+            pe(AMRMG_K_GSRB, (we + (i == 0 ? 0.125 : 0.0)) * n * W + ((mode & 8) ? 16.0 * step_amr_cells(k) : 0.0));
             src = dst;
         }
         if (src != e) launch_copy<T>(st, et + (size_t)b0 * BRICK_CELLS, e + (size_t)b0 * BRICK_CELLS, (int64_t)nb * BRICK_CELLS);
