@@ -1584,17 +1584,16 @@ __global__ void __launch_bounds__(64 * BPW) k_efield(DevMeta M, int b0, int nb, 
     };
     double ex[8], ey[8], ez[8];
     const double h2x = 2.0 * L.h[0], h2y = 2.0 * L.h[1], h2z = 2.0 * L.h[2];
-    const double rx = 1.0 / h2x, ry = 1.0 / h2y, rz = 1.0 / h2z;
     const int kym = y == 0 ? kind[2] : 0, kyp = y == 7 ? kind[3] : 0;
     const int kzm = z == 0 ? kind[4] : 0, kzp = z == 7 ? kind[5] : 0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
         const double um = x == 0 ? ghost(kind[0], a0, hs[0], u[0], u[1]) : u[x - 1];
         const double up = x == 7 ? ghost(kind[1], a0, hs[1], u[7], u[6]) : u[x + 1];
-        ex[x] = -div_by(up - um, h2x, rx);
+        ex[x] = -(up - um) / h2x;
         const double vm = rows[rym + x], vp = rows[ryp + x], wm = rows[rzm + x], wp = rows[rzp + x];
-        ey[x] = -div_by(ghost(kyp, a1, vp, u[x], vm) - ghost(kym, a1, vm, u[x], vp), h2y, ry);
-        ez[x] = -div_by(ghost(kzp, a2, wp, u[x], wm) - ghost(kzm, a2, wm, u[x], wp), h2z, rz);
+        ey[x] = -(ghost(kyp, a1, vp, u[x], vm) - ghost(kym, a1, vm, u[x], vp)) / h2y;
+        ez[x] = -(ghost(kzp, a2, wp, u[x], wm) - ghost(kzm, a2, wm, u[x], wp)) / h2z;
     }
     // out through the rows in LDS, eight lanes a row, so that each store
     // instruction fills whole 64-byte segments
