@@ -83,7 +83,9 @@ typedef dpair dpair_a8 __attribute__((aligned(8)));
 // a / h, correctly rounded, from rh = 1/h rounded to nearest: with the
 // remainder a - h (a rh) exact in one fma, the corrected quotient is the
 // rounded one (Markstein's theorem), in 3 instructions instead of the
-// division's dozen
+// division's dozen.  Only where the quotient, rh and the remainder stay in
+// the normal range: not for infinities, an overflowing quotient or a
+// subnormal h (dep_level scales the domain's extents for that).
 __device__ __forceinline__ double div_by(double a, double h, double rh)
 {
     const double q = a * rh;
@@ -2171,9 +2173,13 @@ __device__ __forceinline__ bool cic_stencil(const DepLevel &D, double X, double 
                                             double *f)
 {
     double xs[3] = {X, Y, Z};
+    // (the level's numbers in one batch of scalar loads, not one an axis after
+    // the axis before)
+    bool in = true;
+    for (int d = 0; d < 3; ++d) in = in & (xs[d] >= D.lo[d]) & (xs[d] < D.hi[d]);
+    if (!in) return false;
     for (int d = 0; d < 3; ++d) {
-        if (!(xs[d] >= D.lo[d] && xs[d] < D.hi[d])) return false;
-        double s = div_by(xs[d] - D.lo[d], D.h[d], D.rh[d]) - 0.5;
+        double s = div_by((xs[d] - D.lo[d]) * D.sc[d], D.hs[d], D.rh[d]) - 0.5;
         double fl = floor(s);
         int a = (int)fl;
         f[d] = s - fl;

@@ -10,8 +10,10 @@ constexpr int MAX_AMR = 8;
 
 // one AMR level as seen by particle kernels
 struct DepLevel {
-    double lo[3], hi[3], h[3];
-    double rh[3];         // 1 / h
+    double lo[3], hi[3];
+    // (x - lo) / h = (x - lo) sc / hs: sc a power of two that brings h among
+    // the ordinary numbers (1 where it is one), hs = h sc, rh = 1 / hs
+    double sc[3], hs[3], rh[3];
     double ivol;          // 1 / (h_x h_y h_z)
     int n[3];             // index extent of the level
     int nbk[3];           // brick grid extent (n / 8)

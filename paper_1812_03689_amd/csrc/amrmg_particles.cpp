@@ -38,8 +38,11 @@ DepLevel dep_level(const Problem &P, const HostLevel &L, const int32_t *bmap)
     for (int d = 0; d < 3; ++d) {
         D.lo[d] = P.lo[d];
         D.hi[d] = P.hi[d];
-        D.h[d] = L.h[d];
-        D.rh[d] = 1.0 / L.h[d];
+        // an extent that overflowed: every position's quotient is 0, as 0 / 1
+        const double h = L.h[d];
+        D.sc[d] = std::isinf(h) ? 0.0 : h < 1e-200 ? 0x1p1000 : h > 1e200 ? 0x1p-700 : 1.0;
+        D.hs[d] = std::isinf(h) ? 1.0 : h * D.sc[d];
+        D.rh[d] = 1.0 / D.hs[d];
         D.n[d] = L.n[d];
         D.nbk[d] = L.nbk[d];
     }
