@@ -713,6 +713,10 @@ __global__ void __launch_bounds__(1024) k_level_norms(const int4 *pieces, const 
             else __hip_atomic_store(psum + p, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
+    // every wavefront waits for its own sum to arrive: the count below orders
+    // (and waits for) the stores of the wavefront that counts alone, and a
+    // barrier waits for no store to memory
+    if (!one) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (!one) {
         if (threadIdx.x == 0) {
