@@ -18,6 +18,7 @@
 #include <cstdlib>
 #include <hip/hip_runtime.h>
 
+#include "amrmg_box.hpp"
 #include "amrmg_internal.hpp"
 #include "amrmg_kernels.hpp"
 
@@ -2240,27 +2241,8 @@ __device__ __forceinline__ int wave_min(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// a box of cells [lo, hi] in LDS, x fastest, and the bricks it spans
-struct DepBox {
-    int lo[3], hi[3];
-    int ex, ey, ez;
-    int bx0, by0, bz0, nbx, nby, nbt;
-    int64_t vol;
-    // v: minima of i0 and of ~i1 per axis
-    __device__ __forceinline__ void set(const int *v)
-    {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            lo[d] = v[d];
-            hi[d] = ~v[3 + d];
-        }
-        ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
-        vol = (int64_t)ex * ey * ez;
-        bx0 = lo[0] >> 3, by0 = lo[1] >> 3, bz0 = lo[2] >> 3;
-        nbx = (hi[0] >> 3) - bx0 + 1, nby = (hi[1] >> 3) - by0 + 1;
-        nbt = nbx * nby * ((hi[2] >> 3) - bz0 + 1);
-    }
-    __device__ __forceinline__ bool empty() const { return lo[0] > hi[0]; }
+// such a box in LDS
+struct DepBox : CellBox {
     // caller's-layout base (-1 outside the level) and strides of brick t of the box
     __device__ __forceinline__ void brick(const DepLevel &D, const int64_t *ubase, const int2 *ustr, int t, int64_t &ub,
                                           int2 &us) const
