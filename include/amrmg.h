@@ -153,7 +153,16 @@ const char *amrmg_last_error(void);
  *                  space, hi exclusive) or NULL; a level with explicit boxes
  *                  is not tagged.  Misaligned or badly nested boxes return
  *                  AMRMG_E_NESTING.
- * Levels with no tagged block end the hierarchy early.  Synchronises. */
+ * Levels with no tagged block end the hierarchy early.  Synchronises.
+ * Memory the context keeps per particle, beside what the hierarchy takes: the
+ * order (8 bytes), its sort (18 to 24), the copy of the particles (8 more than
+ * the positions) and, from 262144 particles, the particles once more as
+ * 32-byte records, which builds, deposits and gathers read in place of the
+ * four arrays.  The records only save time: without room for them the arrays
+ * are read, and they are given back when a later call on the context finds no
+ * room for what it needs (unless a capture has recorded them: then not before
+ * the next build).  Every buffer is allocated a quarter larger than asked for,
+ * grows with the largest build and is freed with the context. */
 amrmg_status amrmg_build_hierarchy(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y,
                                    const void *z, const double *q, int64_t n, const double *tag_rel,
                                    const int32_t *explicit_boxes, int32_t n_explicit);

@@ -651,6 +651,7 @@ extern "C" amrmg_status amrmg_build_hierarchy(amrmg_ctx *ctx, int pos_dtype, con
         }
         expl[e[0]].push_back(B);
     }
+    SpareRecords spare(&ctx);
     ctx->built = false;
     ++ctx->generation;
     // the tagging passes (and amrmg_deposit_built) read the particles in

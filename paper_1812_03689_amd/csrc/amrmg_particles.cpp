@@ -65,6 +65,7 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
     ctx->iperm = nullptr;
     ctx->perm_n = -1;
     ctx->rec = nullptr;
+    ctx->rec_held = false;
     if (n <= 0 || n > (int64_t)0x7fffffff) return AMRMG_OK;
     const amrmg_params &P = ctx->P;
     const size_t sb = order_scratch_bytes(n);
@@ -115,6 +116,9 @@ static const double4 *moved_records(amrmg_ctx *ctx, int pos_dtype, const void *x
                                     const double *q, int64_t n)
 {
     if (n < kPackMin || ctx->perm_n != n || !ctx->rec) return nullptr;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->st, &cap) != hipSuccess) (void)hipGetLastError();
+    else if (cap != hipStreamCaptureStatusNone) ctx->rec_held = true;
     launch_pack_records(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->rec);
     return ctx->rec;
 }
@@ -126,6 +130,7 @@ extern "C" amrmg_status amrmg_deposit(amrmg_ctx *ctx, int pos_dtype, const void 
     if (!ctx->built) return fail(AMRMG_E_STATE, "hierarchy not built");
     if (pos_dtype != AMRMG_POS_F64 && pos_dtype != AMRMG_POS_F32) return fail(AMRMG_E_INVALID, "bad pos_dtype");
     if (!rho || n < 0 || (n > 0 && (!x || !y || !z || !q))) return fail(AMRMG_E_INVALID, "bad arguments");
+    SpareRecords spare(&ctx);
     const Problem &pr = ctx->prob;
     unsigned long long *dout = nullptr;
     if (n_outside) {
@@ -167,6 +172,7 @@ extern "C" amrmg_status amrmg_deposit_built(amrmg_ctx *ctx, double *const *rho, 
     if (!ctx->built) return fail(AMRMG_E_STATE, "hierarchy not built");
     if (ctx->built_n < 0) return fail(AMRMG_E_STATE, "the last build kept no ordered copy of its particles");
     if (!rho) return fail(AMRMG_E_INVALID, "rho is NULL");
+    SpareRecords spare(&ctx);
     const Problem &pr = ctx->prob;
     const int64_t n = ctx->built_n;
     const int pos = ctx->built_pos;
@@ -287,6 +293,7 @@ extern "C" amrmg_status amrmg_gather(amrmg_ctx *ctx, int pos_dtype, const void *
     if (!E || n < 0 || (n > 0 && (!x || !y || !z || !Ex || !Ey || !Ez))) return fail(AMRMG_E_INVALID, "bad arguments");
     GatherArgs G;
     ST_TRY(gather_args(ctx, E, G));
+    SpareRecords spare(&ctx);
     const bool ord = ctx->perm_n == n && n >= kOrderMin;
     double4 *out = ord ? gather_records(ctx, n) : nullptr;
     const double4 *rec = out ? moved_records(ctx, pos_dtype, x, y, z, nullptr, n) : nullptr;
@@ -314,6 +321,7 @@ extern "C" amrmg_status amrmg_gather_built(amrmg_ctx *ctx, double *const *E, dou
     const char *base = (const char *)ctx->sorted.p;
     const char *xs = base + align256((size_t)n * 8), *ys = xs + align256((size_t)n * ps),
                *zs = ys + align256((size_t)n * ps);
+    SpareRecords spare(&ctx);
     double4 *out = n >= kOrderMin ? gather_records(ctx, n) : nullptr;
     ctx->prof.begin(AMRMG_K_GATHER);
     launch_gather(ctx->st, pos == AMRMG_POS_F32, n, xs, ys, zs, nullptr, ctx->perm, ctx->iperm, G, ctx->ds.M.ubase,
@@ -340,6 +348,7 @@ extern "C" amrmg_status amrmg_transform_particles(amrmg_ctx *ctx, int pos_dtype,
     }
     *s = 0.0;
     if (n == 0) return AMRMG_OK;
+    SpareRecords spare(&ctx);
     HIP_TRY(ctx->tag_scratch.ensure(sizeof(double) * 1040));
     unsigned long long *d_bits = (unsigned long long *)ctx->tag_scratch.p;
     HIP_TRY(hipMemsetAsync(d_bits, 0, sizeof(unsigned long long), ctx->st));

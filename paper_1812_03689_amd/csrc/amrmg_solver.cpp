@@ -709,6 +709,7 @@ extern "C" amrmg_status amrmg_solve(amrmg_ctx *ctx, double *const *rho, double *
                                     double tol, amrmg_solve_stats *stats)
 {
     ST_TRY(bind_solve_levels(ctx, rho, phi, E, tol));
+    SpareRecords spare(&ctx);
     ST_TRY(ensure_ws(ctx->ds, ctx->P.precision, ctx->user_ws, ctx->user_ws_bytes));
     return solve_bound(ctx, E != nullptr, tol, stats, false);
 }
@@ -752,6 +753,7 @@ extern "C" amrmg_status amrmg_residual(amrmg_ctx *ctx, double *const *rho, doubl
         D.h_rho[ei] = rho[l];
         D.h_rout[ei] = r[l];
     }
+    SpareRecords spare(&ctx);
     ST_TRY(ensure_ws(D, ctx->P.precision, ctx->user_ws, ctx->user_ws_bytes));
     ST_TRY(set_tables(D, ctx->st));
     SolveOpts o = opts_of(ctx->P);
@@ -783,6 +785,7 @@ extern "C" amrmg_status amrmg_solve_batch(amrmg_ctx *const *ctxs, int32_t nb, do
             return fail(AMRMG_E_INVALID, "context " + std::to_string(i) + ": stream or solver settings differ");
         if (!rho[i] || !phi[i]) return fail(AMRMG_E_INVALID, "rho[i] and phi[i] are required");
     }
+    SpareRecords spare(ctxs, nb);
     // merged metadata of the batch, kept by the first context until one of
     // the contexts builds a new hierarchy
     std::vector<amrmg_ctx *> key(ctxs, ctxs + nb);

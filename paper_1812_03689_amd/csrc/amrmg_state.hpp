@@ -37,6 +37,23 @@ inline size_t align8(size_t x) { return (x + 7) & ~(size_t)7; }
 // grow-only device and pinned host buffers (allocation happens only when a
 // hierarchy outgrows its predecessor, so regrids do not reallocate)
 // ---------------------------------------------------------------------------
+
+// While one of these lives on a thread, a device buffer that finds no room
+// calls it to have buffers given back that only save time, and tries again.
+struct Spare {
+    Spare *outer;
+    static Spare *&current()
+    {
+        static thread_local Spare *s = nullptr;
+        return s;
+    }
+    Spare() : outer(current()) { current() = this; }
+    Spare(const Spare &) = delete;
+    Spare &operator=(const Spare &) = delete;
+    virtual bool give_back() = 0;  // whether anything was
+    ~Spare() { current() = outer; }
+};
+
 struct DBuf {
     void *p = nullptr;
     size_t cap = 0;
@@ -48,6 +65,10 @@ struct DBuf {
         cap = 0;
         size_t c = n + n / 4 + 4096;
         hipError_t e = hipMalloc(&p, c);
+        if (e != hipSuccess && Spare::current() && Spare::current()->give_back()) {
+            (void)hipGetLastError();
+            e = hipMalloc(&p, c);
+        }
         if (e == hipSuccess) cap = c;
         return e;
     }
@@ -305,9 +326,11 @@ struct amrmg_ctx {
     // the particles as records in their own order: written with the sort keys
     // by a build, or from the caller's arrays by a deposit or gather of moved
     // particles, and read through the order (one scattered read a particle);
-    // without room the arrays themselves are read through the order
+    // without room the arrays themselves are read through the order.  rec_held:
+    // a capture has recorded them, they stay until the next build
     DBuf rec_own;
     double4 *rec = nullptr;
+    bool rec_held = false;
     uint32_t *perm = nullptr;
     uint32_t *iperm = nullptr;  // its inverse (perm[iperm[p]] == p)
     int64_t perm_n = -1;
@@ -341,6 +364,27 @@ struct amrmg_ctx {
         delete batch;
         for (auto &e : ev_solve)
             if (e) (void)hipEventDestroy(e);
+    }
+};
+
+// the particle records of nb contexts, given back when a call on them finds
+// no room on the device
+struct SpareRecords : Spare {
+    amrmg_ctx *const *ctxs;
+    int nb;
+    explicit SpareRecords(amrmg_ctx *const *c, int n = 1) : ctxs(c), nb(n) {}
+    bool give_back() override
+    {
+        bool any = false;
+        for (int i = 0; i < nb; ++i) {
+            amrmg_ctx &c = *ctxs[i];
+            if (!c.rec_own.p || c.rec_held) continue;
+            (void)hipStreamSynchronize(c.st);  // a queued deposit or gather may still read them
+            c.rec_own.release();
+            c.rec = nullptr;
+            any = true;
+        }
+        return any;
     }
 };
 
