@@ -367,7 +367,9 @@ amrmg_status amrmg_residual(amrmg_ctx *ctx, double *const *rho, double *const *p
  * phi[i] as in amrmg_solve (no E).  The iteration runs until every problem
  * meets tol; stats host [nb] or NULL gives each problem the iteration at which
  * it met it.  The merged metadata is kept by ctxs[0] and rebuilt when any
- * context builds a new hierarchy or the context list changes. */
+ * context builds a new hierarchy or the context list changes.  Its buffers and
+ * the batch's workspace keep the size of the largest batch until ctxs[0] is
+ * destroyed, or a batch finds no room beside them. */
 amrmg_status amrmg_solve_batch(amrmg_ctx *const *ctxs, int32_t nb, double *const *const *rho,
                                double *const *const *phi, double tol, amrmg_solve_stats *stats);
 

@@ -765,6 +765,19 @@ extern "C" amrmg_status amrmg_residual(amrmg_ctx *ctx, double *const *rho, doubl
     return AMRMG_OK;
 }
 
+// the merged metadata and the workspace of a batch
+static amrmg_status merge_batch(DevState &D, const amrmg_ctx *c0, amrmg_ctx *const *ctxs, int32_t nb)
+{
+    std::vector<const Problem *> probs;
+    for (int i = 0; i < nb; ++i) probs.push_back(&ctxs[i]->prob);
+    ST_TRY(upload_meta(D, c0->st, probs, c0->P.bottom == AMRMG_BOTTOM_AUTO));
+    HIP_TRY(hipStreamSynchronize(c0->st));
+    if (!D.meta.error.empty()) return fail(AMRMG_E_NESTING, D.meta.error);
+    if (*(int *)D.h_face_err.p)
+        return fail(AMRMG_E_NESTING, "coarse-fine window leaves the coarser level (nesting violated)");
+    return ensure_ws(D, c0->P.precision, nullptr, 0);
+}
+
 extern "C" amrmg_status amrmg_solve_batch(amrmg_ctx *const *ctxs, int32_t nb, double *const *const *rho,
                                           double *const *const *phi, double tol, amrmg_solve_stats *stats)
 {
@@ -793,15 +806,19 @@ extern "C" amrmg_status amrmg_solve_batch(amrmg_ctx *const *ctxs, int32_t nb, do
     for (int i = 0; i < nb; ++i) gen[i] = ctxs[i]->generation;
     if (!c0->batch || c0->batch_ctx != key || c0->batch_gen != gen) {
         // (its buffers grow with the batch and are kept, as a context's are)
-        if (!c0->batch) c0->batch = new DevState();
         c0->batch_ctx.clear();
-        std::vector<const Problem *> probs;
-        for (int i = 0; i < nb; ++i) probs.push_back(&ctxs[i]->prob);
-        ST_TRY(upload_meta(*c0->batch, c0->st, probs, c0->P.bottom == AMRMG_BOTTOM_AUTO));
-        HIP_TRY(hipStreamSynchronize(c0->st));
-        if (!c0->batch->meta.error.empty()) return fail(AMRMG_E_NESTING, c0->batch->meta.error);
-        if (*(int *)c0->batch->h_face_err.p)
-            return fail(AMRMG_E_NESTING, "coarse-fine window leaves the coarser level (nesting violated)");
+        bool kept = c0->batch != nullptr;
+        for (;; kept = false) {
+            if (!c0->batch) c0->batch = new DevState();
+            const amrmg_status rc = merge_batch(*c0->batch, c0, ctxs, nb);
+            if (rc == AMRMG_OK) break;
+            if (!kept || (rc != AMRMG_E_HIP && rc != AMRMG_E_OOM)) return rc;
+            // buffers of earlier batches may take the room: once more without them
+            (void)hipGetLastError();
+            HIP_TRY(hipStreamSynchronize(c0->st));
+            delete c0->batch;
+            c0->batch = nullptr;
+        }
         c0->batch_ctx = key;
         c0->batch_gen = gen;
     }
