@@ -42,7 +42,6 @@ size_t ws_need(const DevState &D, int prec)
     s += align256((size_t)m.ncf * 64 * 8 + 8);         // coarse parts of phi
     s += align256((size_t)m.nbrick * 16);              // partial norms (two sets, one per brick)
     s += align256((size_t)m.nbrick * 96 * 8);          // fine sums of the coarse-fine faces
-    s += align256(sizeof(double) * 2 * ((size_t)D.norms.npiece + 1));  // sums of the norms' pieces
     s += align256(D.cg_doubles * 8);
     s += align256(D.dw_doubles * 8 + 8);             // direct-solve scratch
     s += align256(64);
@@ -76,13 +75,15 @@ amrmg_status ensure_ws(DevState &D, int prec, void *user, size_t user_bytes)
     D.e = take(nc * w);
     D.r = take(nc * w);
     D.et = take(nc * w);
+    // the norms' piece sums lie in et, which holds nothing between a V-cycle
+    // and the next (two sums a piece, no more pieces than bricks)
+    D.norms.psum = (double *)D.et;
     D.phib = (double *)take(nc * 8);
     D.rhob = (double *)take(nc * 8);
     D.cpe = take((size_t)m.ncf * 64 * w + 8);
     D.cpphi = (double *)take((size_t)m.ncf * 64 * 8 + 8);
     D.part = (double *)take((size_t)m.nbrick * 16);
     D.ffs = (double *)take((size_t)m.nbrick * 96 * 8);
-    D.norms.psum = (double *)take(sizeof(double) * 2 * ((size_t)D.norms.npiece + 1));
     D.cgw = (double *)take(D.cg_doubles * 8);
     D.dw = (double *)take(D.dw_doubles * 8 + 8);
     D.cgit = (int *)take(64);
