@@ -298,9 +298,10 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     P.add(ed, &dent);
     P.add(bx, &dbox);
     P.add(mono, &dmono);
-    ST_TRY(P.run(D.metabuf, D.stage, st));
-    if (D.dtab_key != tkey || !D.dtabbuf.p) {
-        std::vector<double> dtab;
+    // the direct grids' tables, when they are others than the device has
+    std::vector<double> dtab;
+    const bool new_tab = D.dtab_key != tkey || !D.dtabbuf.p;
+    if (new_tab) {
         dtab.reserve(ntab + 1);
         for (size_t k = 0; k < tkey.size(); k += 9) {
             const int n[3] = {(int)tkey[k], (int)tkey[k + 3], (int)tkey[k + 6]};
@@ -308,10 +309,15 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
             append_padded_tables(dtab, n, cached_direct_tables(n, h, ab));
         }
         if (dtab.empty()) dtab.push_back(0.0);
+    }
+    const size_t tab_bytes = sizeof(double) * dtab.size();
+    ST_TRY(P.run(D.metabuf, D.stage, st, tab_bytes));
+    if (new_tab) {
         D.dtab_key.clear();
-        HIP_TRY(D.dtabbuf.ensure(sizeof(double) * dtab.size()));
-        HIP_TRY(hipMemcpyAsync(D.dtabbuf.p, dtab.data(), sizeof(double) * dtab.size(), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipStreamSynchronize(st));  // (the source ends here)
+        HIP_TRY(D.dtabbuf.ensure(tab_bytes));
+        void *src = (char *)D.stage.p + P.total;
+        std::memcpy(src, dtab.data(), tab_bytes);
+        HIP_TRY(hipMemcpyAsync(D.dtabbuf.p, src, tab_bytes, hipMemcpyHostToDevice, st));
         D.dtab_key = tkey;
     }
     D.d_dtab = (double *)D.dtabbuf.p;

@@ -144,9 +144,10 @@ struct Packer {
         items.push_back({src, bytes, total, dst});
         total += align256(bytes ? bytes : 1);
     }
-    amrmg_status run(DBuf &dev, PBuf &stage, hipStream_t st)
+    // extra: bytes of the staging buffer after the packed ones, for the caller
+    amrmg_status run(DBuf &dev, PBuf &stage, hipStream_t st, size_t extra = 0)
     {
-        HIP_TRY(stage.ensure(total));
+        HIP_TRY(stage.ensure(total + extra));
         HIP_TRY(dev.ensure(total));
         for (auto &it : items) {
             if (it.bytes) std::memcpy((char *)stage.p + it.off, it.src, it.bytes);
