@@ -112,14 +112,17 @@ amrmg_status compute_order(amrmg_ctx *ctx, int pos_dtype, const void *x, const v
 // thousand particles each: 4e6 particles 305 -> 123 us, 1e6 68 -> 33 us, 3e5
 // 13.1 -> 10.4 us, where a launch more is no longer worth it.
 constexpr int64_t kPackMin = (int64_t)1 << 19;
-static const double4 *moved_records(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,
+// cls: the kernel class of the call (its bytes are counted with its own launch)
+static const double4 *moved_records(amrmg_ctx *ctx, int cls, int pos_dtype, const void *x, const void *y, const void *z,
                                     const double *q, int64_t n)
 {
     if (n < kPackMin || ctx->perm_n != n || !ctx->rec) return nullptr;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->st, &cap) != hipSuccess) (void)hipGetLastError();
     else if (cap != hipStreamCaptureStatusNone) ctx->rec_held = true;
+    ctx->prof.begin(cls);
     launch_pack_records(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, ctx->rec);
+    ctx->prof.end(cls, 0.0);
     return ctx->rec;
 }
 
@@ -150,7 +153,7 @@ extern "C" amrmg_status amrmg_deposit(amrmg_ctx *ctx, int pos_dtype, const void 
     launch_set_levels(ctx->st, S, dout);
     int64_t cells = 0;
     for (int l = 0; l < A.nlev; ++l) cells += A.ncell[l];
-    const double4 *rec = moved_records(ctx, pos_dtype, x, y, z, q, n);
+    const double4 *rec = moved_records(ctx, AMRMG_K_DEPOSIT, pos_dtype, x, y, z, q, n);
     ctx->prof.begin(AMRMG_K_DEPOSIT);
     launch_deposit(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, q, rec, ctx->perm_n == n ? ctx->perm : nullptr,
                    A, ctx->ds.M.ubase, ctx->ds.M.ustr, dout, nullptr, nullptr, nullptr, nullptr,
@@ -296,7 +299,7 @@ extern "C" amrmg_status amrmg_gather(amrmg_ctx *ctx, int pos_dtype, const void *
     SpareRecords spare(&ctx);
     const bool ord = ctx->perm_n == n && n >= kOrderMin;
     double4 *out = ord ? gather_records(ctx, n) : nullptr;
-    const double4 *rec = out ? moved_records(ctx, pos_dtype, x, y, z, nullptr, n) : nullptr;
+    const double4 *rec = out ? moved_records(ctx, AMRMG_K_GATHER, pos_dtype, x, y, z, nullptr, n) : nullptr;
     ctx->prof.begin(AMRMG_K_GATHER);
     launch_gather(ctx->st, pos_dtype == AMRMG_POS_F32, n, x, y, z, rec, ord ? ctx->perm : nullptr,
                   ord ? ctx->iperm : nullptr, G, ctx->ds.M.ubase, ctx->ds.M.ustr, Ex, Ey, Ez, out, false,
