@@ -165,7 +165,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         lc[i].amr = m.ent[i].amr;
     }
     // norm ranges: every AMR level of every problem, entry order, in pieces
-    static thread_local std::vector<int32_t> jobs, nfirst;
+    static thread_local std::vector<int32_t> cg_off, nfirst;
     static thread_local std::vector<int4> npieces;
     npieces.clear();
     nfirst.assign(1, 0);
@@ -181,16 +181,12 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
         }
     D.norms.npiece = (int)npieces.size();
     D.norms.n = (int)D.range_prob.size();
-    // bottom solves: the coarsest level of each problem
-    jobs.clear();
+    // bottom solves: four CG vectors of each problem's coarsest level
+    cg_off.clear();
     size_t off = 0;
     for (size_t i = 0; i < m.prob_ent.size(); ++i) {
-        const auto &e = m.ent[m.prob_ent[i][0]];
-        jobs.push_back(e.b0);
-        jobs.push_back(e.nb);
-        jobs.push_back((int32_t)off);
-        jobs.push_back(0);
-        off += (size_t)4 * e.nb * BRICK_CELLS;
+        cg_off.push_back((int32_t)off);
+        off += (size_t)4 * m.ent[m.prob_ent[i][0]].nb * BRICK_CELLS;
     }
     D.njobs = (int)m.prob_ent.size();
     D.cg_doubles = off;
@@ -233,7 +229,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
             cj[i].b0[k] = m.ent[m.prob_ent[i][k]].b0;
             cj[i].nb[k] = m.ent[m.prob_ent[i][k]].nb;
         }
-        cj[i].cg_off = jobs[4 * i + 2];
+        cj[i].cg_off = cg_off[i];
         // direct solve of the coarsest grid when it is one full box of at
         // most DIRECT_DIM cells per axis (the levels below level 0 stop there)
         const auto &e0 = m.ent[m.prob_ent[i][0]];
@@ -279,7 +275,7 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     if (groups.empty()) groups.push_back(make_int2(0, 0));
 
     Packer P;
-    int32_t *dnf = nullptr, *dj = nullptr, *cfi = nullptr;
+    int32_t *dnf = nullptr, *cfi = nullptr;
     int4 *dnp = nullptr;
     uint8_t *cfp = nullptr;
     double *gbc = nullptr;
@@ -287,7 +283,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     P.add(lc, &dlc);
     P.add(npieces, &dnp);
     P.add(nfirst, &dnf);
-    P.add(jobs, &dj);
     P.add(cj, &D.d_cjobs);
     EntryDev *dent = nullptr;
     BoxDev *dbox = nullptr;
@@ -434,7 +429,6 @@ amrmg_status upload_meta(DevState &D, hipStream_t st, const std::vector<const Pr
     D.M.ncf = m.ncf;
     D.norms.pieces = dnp;
     D.norms.first = dnf;
-    D.d_jobs = (int4 *)dj;
     int32_t *dpool = B.pool;
     // the error flag in pinned host memory, written by the kernel where there
     // is an error (what came before in the stream is done: the counts above

@@ -68,8 +68,6 @@ __device__ __forceinline__ int pick_brick(int b0, int nb, const int32_t *list, i
     return list ? list[k] : b0 + k;
 }
 
-__device__ __forceinline__ int oct_of(int x, int y, int z) { return (x >> 2) | ((y >> 2) << 1) | ((z >> 2) << 2); }
-
 __device__ __forceinline__ void transverse(int d, int &du, int &dv)
 {
     du = (d == 0) ? 1 : 0;
@@ -119,10 +117,6 @@ struct OffsetAcc {  // contiguous double slab starting at brick b0
     {
         return u[(size_t)(b - b0) * BRICK_CELLS + l[0] + 8 * l[1] + 64 * l[2]];
     }
-};
-
-struct ZeroAcc {
-    __device__ double operator()(int, const int *) const { return 0.0; }
 };
 
 // The neighbour value that cell l of brick b sees across face (d, s), written
@@ -874,21 +868,6 @@ __global__ void __launch_bounds__(256) k_jacobi(DevMeta M, int b0, int nb, const
         eout[(size_t)b * BRICK_CELLS + c] = (T)(uc + omega * (num / den - uc));
     }
 }
-
-// cycle array plus the injected parent value (prolongation I e^{l-1})
-template <class T>
-struct SrcProl {
-    const T *u;
-    const int32_t *par;
-    __device__ double operator()(int b, int c) const
-    {
-        int p = par[b];
-        int pb = p >> 3, oc = p & 7;
-        int x = c & 7, y = (c >> 3) & 7, z = c >> 6;
-        int pc = ((oc & 1) * 4 + (x >> 1)) + 8 * (((oc >> 1) & 1) * 4 + (y >> 1)) + 64 * ((oc >> 2) * 4 + (z >> 1));
-        return (double)u[(size_t)b * BRICK_CELLS + c] + (double)u[(size_t)pb * BRICK_CELLS + pc];
-    }
-};
 
 // Brick-hybrid Gauss-Seidel sweep: red then black over the cells of one
 // brick in LDS, with the halo taken from the previous sweep (Gauss-Seidel
@@ -2067,17 +2046,6 @@ __global__ void __launch_bounds__(dst_threads(NC)) k_dst_column(const DirectJob 
     }
 }
 
-// one workgroup per job: jobs[i] = (first brick, bricks, offset of its four
-// work vectors in doubles)
-template <class T>
-__global__ void __launch_bounds__(1024) k_bottom_cg(DevMeta M, const int4 *jobs, const T *rhs, T *e, double *work,
-                                                    double rtol, int maxit, int *iters)
-{
-    int4 jb = jobs[blockIdx.x];
-    int it = cg_solve<T>(M, jb.x, jb.y, rhs, e, work + jb.z, rtol, maxit);
-    if (threadIdx.x == 0 && iters) atomicMax(iters, it);
-}
-
 // exact red-black Gauss-Seidel pass over a whole level by one workgroup
 template <class T>
 __device__ void wg_gs_pass(const DevMeta &M, int b0, int nb, T *e, const T *r, int colour)
@@ -2761,23 +2729,6 @@ __global__ void __launch_bounds__(256) k_absmax_part(const double *v, int64_t n,
     if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
-__global__ void __launch_bounds__(256) k_absmax_final(const double *part, int n, double *out)
-{
-    double m = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256) m = fmax(m, part[i]);
-    m = block_reduce(m, 1);
-    if (threadIdx.x == 0) *out = m;
-}
-
-// tag |rho| > lambda * max |rho| (the max read from device memory)
-__global__ void __launch_bounds__(256) k_tag(const double *v, int64_t n, const double *vmax, double lambda,
-                                             uint8_t *tags)
-{
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    tags[i] = fabs(v[i]) > lambda * (*vmax) ? 1 : 0;
-}
-
 template <class T>
 __global__ void __launch_bounds__(256) k_copy(const T *a, T *b, int64_t n)
 {
@@ -2989,14 +2940,6 @@ void launch_efield(hipStream_t st, const DevMeta &M, int b0, int nb, const int32
         AMRMG_LAUNCH((k_efield<1>), dim3(nb), dim3(64), 0, st, M, b0, nb, phib, cp_phi, E, phi, list);
 }
 
-template <class T>
-void launch_bottom_cg(hipStream_t st, const DevMeta &M, const int4 *jobs, int njobs, const T *rhs, T *e,
-                      double *work, double rtol, int maxit, int *iters)
-{
-    if (njobs <= 0) return;
-    AMRMG_LAUNCH((k_bottom_cg<T>), dim3(njobs), dim3(1024), 0, st, M, jobs, rhs, e, work, rtol, maxit, iters);
-}
-
 template <class P, bool REC, int NT, int TILE>
 static void launch_deposit_t(hipStream_t st, int64_t n, const void *x, const void *y, const void *z, const double *q,
                              const double4 *rec, const uint32_t *perm, const DepArgs &A, const int64_t *ubase,
@@ -3077,16 +3020,6 @@ void launch_gather(hipStream_t st, int pos_f32, int64_t n, const void *x, const 
         launch_gather_t<double, 0>(st, n, x, y, z, nullptr, perm, G, ubase, ustr, Ex, Ey, Ez, out, tile);
     }
     if (out) AMRMG_LAUNCH(k_unpermute, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, iperm, out, Ex, Ey, Ez);
-}
-
-void launch_tag(hipStream_t st, const double *v, int64_t n, double lambda, double *scratch, uint8_t *tags)
-{
-    if (n <= 0) return;
-    int parts = (int)blocks_for(n, 256);
-    if (parts > 1024) parts = 1024;
-    AMRMG_LAUNCH(k_absmax_part, dim3(parts), dim3(256), 0, st, v, n, scratch + 1);
-    AMRMG_LAUNCH(k_absmax_final, dim3(1), dim3(256), 0, st, scratch + 1, parts, scratch);
-    AMRMG_LAUNCH(k_tag, dim3(blocks_for(n, 256)), dim3(256), 0, st, v, n, scratch, lambda, tags);
 }
 
 // the size rule: one wavefront (brick) per workgroup
@@ -3238,8 +3171,6 @@ void launch_clear(hipStream_t st, double *v, int64_t n, uint64_t *w, int64_t nw,
     template void launch_prolong<T>(hipStream_t, const DevMeta &, int, int, T *);                                \
     template void launch_phi_update<T>(hipStream_t, const DevMeta &, int, int, const int32_t *, double *,         \
                                        const T *);                                                               \
-    template void launch_bottom_cg<T>(hipStream_t, const DevMeta &, const int4 *, int, const T *, T *, double *, \
-                                      double, int, int *);                                                      \
     template void launch_copy<T>(hipStream_t, const T *, T *, int64_t);                                         \
     template void launch_hgs<T>(hipStream_t, const DevMeta &, int, int, const T *, T *, const T *, T *,         \
                                 double *, double *, int, int);                                                       \

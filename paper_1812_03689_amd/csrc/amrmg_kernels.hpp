@@ -174,9 +174,6 @@ void launch_avgdown(hipStream_t st, const DevMeta &M, int b0, int nb, double *ph
 void launch_efield(hipStream_t st, const DevMeta &M, int b0, int nb, const int32_t *list, const double *phib,
                    const double *cp_phi, double *const *E, double *const *phi);
 template <class T>
-void launch_bottom_cg(hipStream_t st, const DevMeta &M, const int4 *jobs, int njobs, const T *rhs, T *e,
-                      double *work, double rtol, int maxit, int *iters);
-template <class T>
 void launch_copy(hipStream_t st, const T *a, T *b, int64_t n);
 // brick-hybrid Gauss-Seidel sweep; mode = bits of HG_ZERO 1, HG_PROL 2, HG_CPIN 4, HG_PHI 8,
 // HG_FFS 16 (fine sums of the result into ffs)
@@ -234,7 +231,6 @@ void launch_gather(hipStream_t st, int pos_f32, int64_t n, const void *x, const 
                    const double4 *rec, const uint32_t *perm, const uint32_t *iperm, const GatherArgs &G,
                    const int64_t *ubase, const int2 *ustr, double *Ex, double *Ey, double *Ez, double4 *out,
                    bool ordered = false, bool tile = false);
-void launch_tag(hipStream_t st, const double *v, int64_t n, double lambda, double *scratch, uint8_t *tags);
 // spatial visiting order of the particles (stable radix sort by the
 // Morton code of their cell on a sort grid: the level-0 grid n0 refined
 // towards about four particles per cell but at most levels times, at most

@@ -181,7 +181,6 @@ struct DevState {
     int32_t *d_reflux = nullptr, *d_amr = nullptr;
     NormPlan norms{};  // over the AMR levels of every problem
     std::vector<int> range_prob, range_amr;
-    int4 *d_jobs = nullptr;
     int njobs = 0;
     size_t cg_doubles = 0;
     CoarseJob *d_cjobs = nullptr;
