@@ -130,7 +130,8 @@ void launch_user_brick(hipStream_t st, const DevMeta &M, int b0, int nb, const i
                        double *const *a, double *ab, double *const *bu, double *bb);
 // The ranges whose norms a solve wants, cut into pieces of at most NORM_PIECE
 // bricks: pieces (first brick, bricks, range), first[j] .. first[j + 1] those
-// of range j; psum [2 npiece] and done (zero between launches) are scratch
+// of range j; psum [2 npiece] and done (zero between launches) are scratch of a
+// launch
 constexpr int NORM_PIECE = 512, NORM_ONE = 64;
 struct NormPlan {
     const int4 *pieces;

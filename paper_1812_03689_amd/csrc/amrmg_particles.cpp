@@ -284,7 +284,10 @@ static bool dense_gather(const amrmg_ctx *ctx, int64_t n)
 // A gather of fewer particles than this visits them in the caller's order
 // (the field is in the caches anyway) and writes E at its place, one launch:
 // 5e4 particles on 32^3 + 1 levels 10.1 -> 8.7 us, on 64^3 + 2 14.4 -> 14.6;
-// 1e5 14.0 -> 11.6 and 19.0 -> 19.5; 2e5 on 64^3 + 2 24.8 -> 30.3.
+// 1e5 14.0 -> 11.6 and 19.0 -> 19.5; 2e5 on 64^3 + 2 24.8 -> 30.3.  Against
+// the two launches with everything flushed from the caches before each call:
+// 5e4 moved particles 15.1 -> 12.5 and 21.7 -> 19.5, the build's 14.7 -> 12.2
+// and 21.4 -> 22.9 (right after a solve 24.1 -> 14.2 and 30.5 -> 21.0).
 constexpr int64_t kOrderMin = (int64_t)1 << 16;
 
 extern "C" amrmg_status amrmg_gather(amrmg_ctx *ctx, int pos_dtype, const void *x, const void *y, const void *z,

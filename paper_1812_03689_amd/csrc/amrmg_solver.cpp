@@ -459,7 +459,7 @@ struct SolveTimers {
 // (two are made for this solve).  noalloc: the solve may allocate nothing --
 // no sweep tuning (the tuned or the size rule's threads per brick), the
 // events of ev_fixed.  The kernels of an iteration are launched one by one:
-// the host keeps ahead of the GPU (20 launches against 130 us at 64^3 + 2
+// the host keeps ahead of the GPU (18 launches against 115 us at 64^3 + 2
 // levels), while a captured graph costs its capture and instantiation after
 // every build (50 us, 130 for a batch of sixteen) and some 5 us at its
 // boundary each iteration: 32^3 + 1 step 717 -> 655 us, 64^3 + 2 step 1522 ->
